@@ -73,22 +73,57 @@ __device__ __forceinline__ void vstore(V* p, V v) {
     else *p = v;
 }
 
-// ---- fp32 lanes: FULL = all 4 coordinates valid, else the first n --------
+// ---- a lane's 4 coordinates ------------------------------------------------
+//
+// A lane covers up to 4 coordinates of a row of P, of which n = min(4, P - p)
+// exist (n may be zero or negative for lanes of a ragged block past the row's
+// end).  Three ways to move them:
+//   kFull    n = 4 for every lane of the wavefront: 128-bit (bf16: 64-bit)
+//            accesses.
+//   kRagged  P >= 4, the row's last wavefront: every lane loads 4 existing
+//            coordinates with one access, the ones past the end taking the
+//            row's last 4 (aligned to the element only) and shifting theirs
+//            into place; what they load of other lanes' coordinates, which
+//            those may already have updated, is dropped.  Loading the short lane's coordinates one by one
+//            behind a branch made a wave wait for each before it issued the
+//            next, W round trips to memory in a row (reconcile of 8 x 100,003
+//            bf16 coordinates: 15.0 us, so 8.9, both with the
+//            thread-per-coordinate kernel).
+//   kTiny    P < 4: one by one, the missing ones taking the last coordinate.
+// Nothing computed from a missing coordinate is stored.
+enum Lanes { kTiny, kFull, kRagged };
 
-template <bool FULL, bool NT>
+typedef float f32x4_el __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint32_t u32x2_el __attribute__((ext_vector_type(2), aligned(2)));
+
+__device__ __forceinline__ int tail_index(int k, int n) { return k < n ? k : n - 1; }
+
+// x[k] <- x[k + shift] (the last one past the end)
+__device__ __forceinline__ void shift_down(int shift, float (&x)[kVec]) {
+    const float a = x[0], b = x[1], c = x[2], d = x[3];
+    x[0] = shift == 0 ? a : shift == 1 ? b : shift == 2 ? c : d;
+    x[1] = shift == 0 ? b : shift == 1 ? c : d;
+    x[2] = shift == 0 ? c : d;
+}
+
+template <int F, bool NT>
 __device__ __forceinline__ void load_f32(const float* p, int n, float (&x)[kVec]) {
-    if constexpr (FULL) {
+    if constexpr (F == kFull) {
         f32x4 v = vload<NT>(reinterpret_cast<const f32x4*>(p));
         x[0] = v.x; x[1] = v.y; x[2] = v.z; x[3] = v.w;
+    } else if constexpr (F == kRagged) {
+        const f32x4_el v = vload<NT>(reinterpret_cast<const f32x4_el*>(p - (kVec - n)));
+        x[0] = v.x; x[1] = v.y; x[2] = v.z; x[3] = v.w;
+        shift_down(kVec - n, x);
     } else {
 #pragma unroll
-        for (int k = 0; k < kVec; ++k) x[k] = k < n ? p[k] : 0.0f;
+        for (int k = 0; k < kVec; ++k) x[k] = p[tail_index(k, n)];
     }
 }
 
-template <bool FULL, bool NT>
+template <int F, bool NT>
 __device__ __forceinline__ void store_f32(float* p, int n, const float (&x)[kVec]) {
-    if constexpr (FULL) {
+    if (F == kFull || (F == kRagged && n == kVec)) {
         f32x4 v = {x[0], x[1], x[2], x[3]};
         vstore<NT>(reinterpret_cast<f32x4*>(p), v);
     } else {
@@ -98,18 +133,30 @@ __device__ __forceinline__ void store_f32(float* p, int n, const float (&x)[kVec
     }
 }
 
+// body(lanes, n) with the way the calling wavefront's lanes move their
+// coordinates p0 .. p0 + n - 1 of a row of P (p0 is its lane's first)
+template <class Body>
+__device__ __forceinline__ void for_lanes(int64_t p0, int64_t P, Body body) {
+    if (__all(p0 + kVec <= P))
+        body(std::integral_constant<int, kFull>(), kVec);
+    else if (P >= kVec)
+        body(std::integral_constant<int, kRagged>(), (int)min(P - p0, (int64_t)kVec));
+    else
+        body(std::integral_constant<int, kTiny>(), (int)min(P - p0, (int64_t)kVec));
+}
+
 // ---- parameter storage ----------------------------------------------------
 
 struct ParamF32 {
     using T = float;
     __device__ static __forceinline__ float round(float x) { return x; }
-    template <bool FULL, bool NT>
+    template <int F, bool NT>
     __device__ static __forceinline__ void load(const T* p, int n, float (&x)[kVec]) {
-        load_f32<FULL, NT>(p, n, x);
+        load_f32<F, NT>(p, n, x);
     }
-    template <bool FULL, bool NT>
+    template <int F, bool NT>
     __device__ static __forceinline__ void store(T* p, int n, const float (&x)[kVec]) {
-        store_f32<FULL, NT>(p, n, x);
+        store_f32<F, NT>(p, n, x);
     }
 };
 
@@ -125,22 +172,27 @@ __device__ __forceinline__ float bf16_value(uint32_t h) { return __uint_as_float
 struct ParamBF16 {
     using T = uint16_t;
     __device__ static __forceinline__ float round(float x) { return bf16_value(bf16_bits(x)); }
-    template <bool FULL, bool NT>
+    template <int F, bool NT>
     __device__ static __forceinline__ void load(const T* p, int n, float (&x)[kVec]) {
-        if constexpr (FULL) {
-            u32x2 v = vload<NT>(reinterpret_cast<const u32x2*>(p));
+        if constexpr (F != kTiny) {
+            u32x2 v;
+            if constexpr (F == kFull)
+                v = vload<NT>(reinterpret_cast<const u32x2*>(p));
+            else
+                v = vload<NT>(reinterpret_cast<const u32x2_el*>(p - (kVec - n)));
             x[0] = __uint_as_float(v.x << 16);
             x[1] = __uint_as_float(v.x & 0xFFFF0000u);
             x[2] = __uint_as_float(v.y << 16);
             x[3] = __uint_as_float(v.y & 0xFFFF0000u);
+            if constexpr (F == kRagged) shift_down(kVec - n, x);
         } else {
 #pragma unroll
-            for (int k = 0; k < kVec; ++k) x[k] = k < n ? bf16_value(p[k]) : 0.0f;
+            for (int k = 0; k < kVec; ++k) x[k] = bf16_value(p[tail_index(k, n)]);
         }
     }
-    template <bool FULL, bool NT>
+    template <int F, bool NT>
     __device__ static __forceinline__ void store(T* p, int n, const float (&x)[kVec]) {
-        if constexpr (FULL) {
+        if (F == kFull || (F == kRagged && n == kVec)) {
             u32x2 v = {bf16_bits(x[0]) | (bf16_bits(x[1]) << 16),
                        bf16_bits(x[2]) | (bf16_bits(x[3]) << 16)};
             vstore<NT>(reinterpret_cast<u32x2*>(p), v);
@@ -185,6 +237,19 @@ __device__ __forceinline__ float opt_update(const OptParams& o, float th, float&
         v = fmaf(o.omb2, g * g, o.beta2 * v);
         const float denom = sqrtf(v) / o.sqrt_bc2 + o.eps;
         return PS::round(fmaf(-o.step_size, m / denom, t));
+    }
+}
+
+// SlowMo outer step of 4 coordinates, s the sum of x_i - a:
+//   u <- beta u + (a - avg)/lr ;  a <- a - alpha lr u
+__device__ __forceinline__ void slowmo_step(float beta, float alpha_lr, float lr, float inv_w,
+                                            const float (&s)[kVec], float (&u)[kVec],
+                                            float (&a)[kVec]) {
+#pragma unroll
+    for (int k = 0; k < kVec; ++k) {
+        const float drift = s[k] * inv_w;  // avg - a
+        u[k] = fmaf(beta, u[k], -drift / lr);
+        a[k] = fmaf(-alpha_lr, u[k], a[k]);
     }
 }
 
@@ -284,20 +349,20 @@ __device__ __forceinline__ int64_t local_cell(int64_t cells) {
 
 // ---- local step: one replica row per block, 4 coordinates per thread -------
 
-template <Opt O, class PS, class GS, class MS, bool FULL>
+template <Opt O, class PS, class GS, class MS, int F>
 __device__ __forceinline__ void local_chunk(const OptParams& o, typename PS::T* params,
                                             typename MS::T* mom, float* mom2,
                                             const typename GS::T* grads, int n) {
     float g[kVec], m[kVec], v[kVec] = {0.0f, 0.0f, 0.0f, 0.0f}, th[kVec];
-    GS::template load<FULL, kNTL>(grads, n, g);
-    MS::template load<FULL, kNTL>(mom, n, m);
-    if constexpr (O == Opt::ADAMW) load_f32<FULL, kNTL>(mom2, n, v);
-    PS::template load<FULL, kNTL>(params, n, th);
+    GS::template load<F, kNTL>(grads, n, g);
+    MS::template load<F, kNTL>(mom, n, m);
+    if constexpr (O == Opt::ADAMW) load_f32<F, kNTL>(mom2, n, v);
+    PS::template load<F, kNTL>(params, n, th);
 #pragma unroll
     for (int k = 0; k < kVec; ++k) th[k] = opt_update<O, PS, MS>(o, th[k], m[k], v[k], g[k]);
-    MS::template store<FULL, kNTS>(mom, n, m);
-    if constexpr (O == Opt::ADAMW) store_f32<FULL, kNTS>(mom2, n, v);
-    PS::template store<FULL, kNTS>(params, n, th);
+    MS::template store<F, kNTS>(mom, n, m);
+    if constexpr (O == Opt::ADAMW) store_f32<F, kNTS>(mom2, n, v);
+    PS::template store<F, kNTS>(params, n, th);
 }
 
 template <Opt O, class PS, class GS = ParamF32, class MS = ParamF32>
@@ -305,12 +370,9 @@ __device__ __forceinline__ void local_dispatch(const OptParams& o, typename PS::
                                                typename MS::T* mom, float* mom2,
                                                const typename GS::T* grads, int64_t p0,
                                                int64_t P) {
-    if (p0 + kVec <= P)
-        local_chunk<O, PS, GS, MS, true>(o, params + p0, mom + p0, mom2 + p0, grads + p0,
-                                         kVec);
-    else
-        local_chunk<O, PS, GS, MS, false>(o, params + p0, mom + p0, mom2 + p0, grads + p0,
-                                          (int)(P - p0));
+    for_lanes(p0, P, [&](auto lanes, int n) {
+        local_chunk<O, PS, GS, MS, lanes>(o, params + p0, mom + p0, mom2 + p0, grads + p0, n);
+    });
 }
 
 // ---- fused synchronisation steps ----------------------------------------------
@@ -355,20 +417,20 @@ struct SyncAcc {
     float vsum[kVec];
 };
 
-template <int C, bool FULL, class Rows>
+template <int C, int F, class Rows>
 __device__ __forceinline__ void grad_batch(const Rows& r, int i0, int64_t p0, int n,
                                            float (&acc)[kVec]) {
     float g[C][kVec];
 #pragma unroll
     for (int c = 0; c < C; ++c)
-        Rows::GS::template load<FULL, kNTL>(r.g(i0 + c) + p0, n, g[c]);
+        Rows::GS::template load<F, kNTL>(r.g(i0 + c) + p0, n, g[c]);
 #pragma unroll
     for (int c = 0; c < C; ++c)
 #pragma unroll
         for (int k = 0; k < kVec; ++k) acc[k] += g[c][k];
 }
 
-template <Sync M, Opt O, int C, class PS, bool FULL, class Rows>
+template <Sync M, Opt O, int C, class PS, int F, class Rows>
 __device__ __forceinline__ void step_batch(const OptParams& o, const Rows& r, int i0, int64_t p0,
                                            int n, SyncAcc& z, bool avg_state) {
     constexpr bool kAdam = O == Opt::ADAMW;
@@ -376,10 +438,10 @@ __device__ __forceinline__ void step_batch(const OptParams& o, const Rows& r, in
 #pragma unroll
     for (int c = 0; c < C; ++c) {
         if constexpr (M == Sync::LocalSGD)
-            Rows::GS::template load<FULL, kNTL>(r.g(i0 + c) + p0, n, g[c]);
-        Rows::MS::template load<FULL, kNTL>(r.m(i0 + c) + p0, n, m[c]);
-        if constexpr (kAdam) load_f32<FULL, kNTL>(r.v(i0 + c) + p0, n, v[c]);
-        PS::template load<FULL, kNTL>(r.prm(i0 + c) + p0, n, th[c]);
+            Rows::GS::template load<F, kNTL>(r.g(i0 + c) + p0, n, g[c]);
+        Rows::MS::template load<F, kNTL>(r.m(i0 + c) + p0, n, m[c]);
+        if constexpr (kAdam) load_f32<F, kNTL>(r.v(i0 + c) + p0, n, v[c]);
+        PS::template load<F, kNTL>(r.prm(i0 + c) + p0, n, th[c]);
     }
 #pragma unroll
     for (int c = 0; c < C; ++c)
@@ -406,14 +468,14 @@ __device__ __forceinline__ void step_batch(const OptParams& o, const Rows& r, in
                 if constexpr (kAdam) z.vsum[k] += v[c][k];
             }
         } else {
-            Rows::MS::template store<FULL, kNTS>(r.m(i0 + c) + p0, n, m[c]);
-            if constexpr (kAdam) store_f32<FULL, kNTS>(r.v(i0 + c) + p0, n, v[c]);
+            Rows::MS::template store<F, kNTS>(r.m(i0 + c) + p0, n, m[c]);
+            if constexpr (kAdam) store_f32<F, kNTS>(r.v(i0 + c) + p0, n, v[c]);
         }
-        if constexpr (M == Sync::DDP) PS::template store<FULL, kNTS>(r.prm(i0 + c) + p0, n, th[c]);
+        if constexpr (M == Sync::DDP) PS::template store<F, kNTS>(r.prm(i0 + c) + p0, n, th[c]);
     }
 }
 
-template <Sync M, Opt O, int WT, class PS, bool FULL, bool EXTRA, class Rows>
+template <Sync M, Opt O, int WT, class PS, int F, bool EXTRA, class Rows>
 __device__ __forceinline__ void sync_chunk(const OptParams& o, const Rows& r, float* slow,
                                            float* anchor, int W, int64_t p0, int n, float beta,
                                            float alpha_lr, float inv_w, unsigned flags) {
@@ -434,22 +496,22 @@ __device__ __forceinline__ void sync_chunk(const OptParams& o, const Rows& r, fl
         float acc[kVec] = {0.0f, 0.0f, 0.0f, 0.0f};
         if constexpr (WT > 0) {
 #pragma unroll
-            for (int i0 = 0; i0 < WT; i0 += C) grad_batch<C, FULL>(r, i0, p0, n, acc);
+            for (int i0 = 0; i0 < WT; i0 += C) grad_batch<C, F>(r, i0, p0, n, acc);
         } else {
             int i0 = 0;
-            for (; i0 + C <= nw; i0 += C) grad_batch<C, FULL>(r, i0, p0, n, acc);
-            for (; i0 < nw; ++i0) grad_batch<1, FULL>(r, i0, p0, n, acc);
+            for (; i0 + C <= nw; i0 += C) grad_batch<C, F>(r, i0, p0, n, acc);
+            for (; i0 < nw; ++i0) grad_batch<1, F>(r, i0, p0, n, acc);
         }
 #pragma unroll
         for (int k = 0; k < kVec; ++k) z.gbar[k] = acc[k] * inv_w;
         if (EXTRA && (flags & kSyncWriteGbar))
             for (int i = 0; i < nw; ++i)
-                Rows::GS::template store<FULL, kNTS>(r.g(i) + p0, n, z.gbar);
+                Rows::GS::template store<F, kNTS>(r.g(i) + p0, n, z.gbar);
     }
 
     if constexpr (M == Sync::CPDP) {
-        load_f32<FULL, kNTL>(anchor + p0, n, z.a);
-        load_f32<FULL, kNTL>(slow + p0, n, z.u);
+        load_f32<F, kNTL>(anchor + p0, n, z.a);
+        load_f32<F, kNTL>(slow + p0, n, z.u);
     }
 
     // optimizer step of every replica.  The parameter mean is accumulated as
@@ -458,11 +520,11 @@ __device__ __forceinline__ void sync_chunk(const OptParams& o, const Rows& r, fl
     // keep their precision.
     if constexpr (WT > 0) {
 #pragma unroll
-        for (int i0 = 0; i0 < WT; i0 += C) step_batch<M, O, C, PS, FULL>(o, r, i0, p0, n, z, avg_state);
+        for (int i0 = 0; i0 < WT; i0 += C) step_batch<M, O, C, PS, F>(o, r, i0, p0, n, z, avg_state);
     } else {
         int i0 = 0;
-        for (; i0 + C <= nw; i0 += C) step_batch<M, O, C, PS, FULL>(o, r, i0, p0, n, z, avg_state);
-        for (; i0 < nw; ++i0) step_batch<M, O, 1, PS, FULL>(o, r, i0, p0, n, z, avg_state);
+        for (; i0 + C <= nw; i0 += C) step_batch<M, O, C, PS, F>(o, r, i0, p0, n, z, avg_state);
+        for (; i0 < nw; ++i0) step_batch<M, O, 1, PS, F>(o, r, i0, p0, n, z, avg_state);
     }
     if (avg_state) {
 #pragma unroll
@@ -471,31 +533,25 @@ __device__ __forceinline__ void sync_chunk(const OptParams& o, const Rows& r, fl
             z.vsum[k] *= inv_w;
         }
         for (int i = 0; i < nw; ++i) {
-            Rows::MS::template store<FULL, kNTS>(r.m(i) + p0, n, z.msum);
-            if constexpr (kAdam) store_f32<FULL, kNTS>(r.v(i) + p0, n, z.vsum);
+            Rows::MS::template store<F, kNTS>(r.m(i) + p0, n, z.msum);
+            if constexpr (kAdam) store_f32<F, kNTS>(r.v(i) + p0, n, z.vsum);
         }
     }
     if constexpr (M == Sync::DDP) return;
 
     if constexpr (M == Sync::CPDP) {
-        // SlowMo outer step: u <- beta u + (a - avg)/lr ; new = a - alpha lr u
-#pragma unroll
-        for (int k = 0; k < kVec; ++k) {
-            const float drift = z.s[k] * inv_w;  // avg - a
-            z.u[k] = fmaf(beta, z.u[k], -drift / o.lr);
-            z.a[k] = fmaf(-alpha_lr, z.u[k], z.a[k]);
-        }
-        store_f32<FULL, kNTS>(slow + p0, n, z.u);
-        store_f32<FULL, kNTS>(anchor + p0, n, z.a);
+        slowmo_step(beta, alpha_lr, o.lr, inv_w, z.s, z.u, z.a);
+        store_f32<F, kNTS>(slow + p0, n, z.u);
+        store_f32<F, kNTS>(anchor + p0, n, z.a);
     } else {
 #pragma unroll
         for (int k = 0; k < kVec; ++k) z.a[k] = fmaf(z.s[k], inv_w, z.x0[k]);
-        if (anchor != nullptr) store_f32<FULL, kNTS>(anchor + p0, n, z.a);
+        if (anchor != nullptr) store_f32<F, kNTS>(anchor + p0, n, z.a);
     }
 
     // copy the reconciled model back into every replica
 #pragma unroll
-    for (int i = 0; i < nw; ++i) PS::template store<FULL, kNTS>(r.prm(i) + p0, n, z.a);
+    for (int i = 0; i < nw; ++i) PS::template store<F, kNTS>(r.prm(i) + p0, n, z.a);
 }
 
 // The gradient rows are written only by the variants (the gradient-mean

@@ -49,12 +49,10 @@ __global__ __launch_bounds__(kBlock) void sync_plan_kernel(Src src,
     const Table<PS> r{v.params, v.mom, v.mom2, v.grads, n, t};
     float* slow = reinterpret_cast<float*>(v.slow[t]);
     float* anchor = reinterpret_cast<float*>(v.anchor[t]);
-    if (p0 + kVec <= P)
-        sync_chunk<M, O, 0, PS, true, EXTRA>(e.o, r, slow, anchor, W, p0, kVec, e.beta,
-                                             e.alpha_lr, inv_w, flags);
-    else
-        sync_chunk<M, O, 0, PS, false, EXTRA>(e.o, r, slow, anchor, W, p0, (int)(P - p0),
-                                              e.beta, e.alpha_lr, inv_w, flags);
+    for_lanes(p0, P, [&](auto lanes, int n) {
+        sync_chunk<M, O, 0, PS, lanes, EXTRA>(e.o, r, slow, anchor, W, p0, n, e.beta, e.alpha_lr,
+                                              inv_w, flags);
+    });
 }
 
 template <Opt O, class Src>

@@ -5,6 +5,7 @@
 #pragma once
 
 #include "cpdp_device.h"
+#include "cpdp_split.h"
 
 namespace cpdp {
 namespace {
@@ -20,12 +21,10 @@ __global__ __launch_bounds__(kBlock) void sync_kernel(
     // Strided holds mutable row pointers; without EXTRA no store to the
     // gradient rows is instantiated
     const Strided<PS, GS, MS> r{params, mom, mom2, const_cast<typename GS::T*>(grads), ld};
-    if (p0 + kVec <= P)
-        sync_chunk<M, O, WT, PS, true, EXTRA>(o, r, slow, anchor, W, p0, kVec, beta, alpha_lr,
-                                              inv_w, flags);
-    else
-        sync_chunk<M, O, WT, PS, false, EXTRA>(o, r, slow, anchor, W, p0, (int)(P - p0), beta,
-                                               alpha_lr, inv_w, flags);
+    for_lanes(p0, P, [&](auto lanes, int n) {
+        sync_chunk<M, O, WT, PS, lanes, EXTRA>(o, r, slow, anchor, W, p0, n, beta, alpha_lr, inv_w,
+                                               flags);
+    });
 }
 
 template <Sync M, Opt O, int WT, class PS, bool EXTRA = false, class GS = ParamF32,
@@ -43,20 +42,49 @@ int sync_w(const OptParams& o, const SyncArgs& a) {
                   a.slow, a.anchor, a.W, a.ld, a.P, a.beta, alpha_lr, inv_w, a.flags);
 }
 
+// Which kernel takes the step.  The split one, except
+//  * W outside its range (W = 1 and 2, and more than 32 replicas);
+//  * fp32 momentum SGD on 4, 8 or 16 replicas when the rows stay in the 256 MB
+//    last-level cache from one call to the next and the thread-per-coordinate
+//    kernel has a wavefront for every SIMD (1024 of them): the blocks of the
+//    split kernel then run in a few rounds that load and store in step, and
+//    that kernel is 3-17 % faster (W = 8, 262,144 coordinates: 7.7 against
+//    8.2 us; W = 16: 13.2 against 16.0).  With fewer wavefronts its serial
+//    batches cost more (W = 8, 65,539: 4.3 against 3.9), and past the cache
+//    the split kernel streams faster (W = 16, 800,001: 52.6 against 46.3);
+//  * a DDP step that writes the gradient mean back, past the cache: it streams
+//    as many rows in as out and the two are level to 2 % in favour of the
+//    thread-per-coordinate kernel (W = 6, 11.2 M: 290 against 296 us); on a
+//    small state the split one is twice as fast.
+constexpr int64_t kCachedElems = (int64_t)1 << 23;  // W * P: 168 MB of fp32 momentum SGD rows
+
+template <Sync M, Opt O, class PS, class GS, class MS>
+constexpr bool kPlainRows = O != Opt::ADAMW && std::is_same<PS, ParamF32>::value &&
+                            std::is_same<GS, ParamF32>::value && std::is_same<MS, ParamF32>::value;
+
 template <Sync M, Opt O, class PS, class GS = ParamF32, class MS = ParamF32>
 int sync_t(const OptParams& o, const SyncArgs& a) {
+    constexpr bool plain = kPlainRows<M, O, PS, GS, MS>;
+    const DirectScalars src{o, a.beta, a.alpha * o.lr};
+    const bool cached = a.P < kCachedElems / a.W;
     if constexpr (std::is_same<GS, ParamF32>::value && std::is_same<MS, ParamF32>::value) {
-        if (a.flags != 0) return sync_w<M, O, 0, PS, true>(o, a);
+        if (a.flags != 0) {
+            const bool split = M != Sync::DDP || !(a.flags & kSyncWriteGbar) || cached;
+            return can_split(a.W) && split ? sync_split<M, O, PS, true, GS, MS>(src, a)
+                                           : sync_w<M, O, 0, PS, true>(o, a);
+        }
     }
-    switch (a.W) {
-        case 1: return sync_w<M, O, 1, PS, false, GS, MS>(o, a);
-        case 2: return sync_w<M, O, 2, PS, false, GS, MS>(o, a);
-        case 4: return sync_w<M, O, 4, PS, false, GS, MS>(o, a);
-        case 8: return sync_w<M, O, 8, PS, false, GS, MS>(o, a);
-        case 16: return sync_w<M, O, 16, PS, false, GS, MS>(o, a);
-        case 32: return sync_w<M, O, 32, PS, false, GS, MS>(o, a);
-        default: return sync_w<M, O, 0, PS, false, GS, MS>(o, a);
+    if (a.W == 1) return sync_w<M, O, 1, PS, false, GS, MS>(o, a);
+    if (a.W == 2) return sync_w<M, O, 2, PS, false, GS, MS>(o, a);
+    if constexpr (plain) {
+        if (cached && blocks_for(a.P) >= 1024) {
+            if (a.W == 4) return sync_w<M, O, 4, PS, false, GS, MS>(o, a);
+            if (a.W == 8) return sync_w<M, O, 8, PS, false, GS, MS>(o, a);
+            if (a.W == 16) return sync_w<M, O, 16, PS, false, GS, MS>(o, a);
+        }
     }
+    if (can_split(a.W)) return sync_split<M, O, PS, false, GS, MS>(src, a);
+    return sync_w<M, O, 0, PS, false, GS, MS>(o, a);
 }
 
 // bf16 gradients or momentum: momentum SGD without variants only (the

@@ -18,17 +18,17 @@ __device__ __forceinline__ bool same_stored(float a, float b) {
     return __float_as_uint(a) == __float_as_uint(b);
 }
 
-template <class PS, bool FULL>
+template <class PS, int F>
 __device__ __forceinline__ unsigned long long count_chunk(const typename PS::T* params,
                                                           const float* anchor, int W, int64_t ld,
                                                           int64_t p0, int n) {
     float a[kVec], x[kVec];
     bool differs[kVec] = {false, false, false, false};
-    load_f32<FULL, false>(anchor + p0, n, a);
+    load_f32<F, false>(anchor + p0, n, a);
 #pragma unroll
     for (int k = 0; k < kVec; ++k) a[k] = PS::round(a[k]);
     for (int i = 0; i < W; ++i) {
-        PS::template load<FULL, false>(params + (int64_t)i * ld + p0, n, x);
+        PS::template load<F, false>(params + (int64_t)i * ld + p0, n, x);
 #pragma unroll
         for (int k = 0; k < kVec; ++k) differs[k] = differs[k] || !same_stored(x[k], a[k]);
     }
@@ -44,10 +44,10 @@ __global__ __launch_bounds__(kBlock) void count_unsynced_kernel(
     int64_t ld, int64_t P, unsigned long long* __restrict__ count) {
     const int64_t p0 = ((int64_t)blockIdx.x * kBlock + threadIdx.x) * kVec;
     unsigned long long bad = 0;
-    if (p0 + kVec <= P)
-        bad = count_chunk<PS, true>(params, anchor, W, ld, p0, kVec);
-    else if (p0 < P)
-        bad = count_chunk<PS, false>(params, anchor, W, ld, p0, (int)(P - p0));
+    if (p0 < P)
+        for_lanes(p0, P, [&](auto lanes, int n) {
+            bad = count_chunk<PS, lanes>(params, anchor, W, ld, p0, n);
+        });
     // every lane takes part in the shuffles, including those past P
     for (int off = warpSize / 2; off > 0; off >>= 1) bad += __shfl_xor(bad, off);
     if ((threadIdx.x % warpSize) == 0 && bad != 0) atomicAdd(count, bad);

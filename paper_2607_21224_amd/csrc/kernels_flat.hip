@@ -8,21 +8,21 @@ namespace {
 
 // ---- state initialisation ---------------------------------------------------
 
-template <class PS, class MS, bool FULL>
+template <class PS, class MS, int F>
 __device__ __forceinline__ void init_chunk(const typename PS::T* theta0, typename PS::T* params,
                                            typename MS::T* mom, float* mom2, float* slow,
                                            float* anchor, int W, int64_t ld, int64_t p0, int n) {
     float th[kVec];
     const float zero[kVec] = {0.0f, 0.0f, 0.0f, 0.0f};
-    PS::template load<FULL, false>(theta0 + p0, n, th);
+    PS::template load<F, false>(theta0 + p0, n, th);
     for (int i = 0; i < W; ++i) {
         const int64_t off = (int64_t)i * ld + p0;
-        PS::template store<FULL, kNTS>(params + off, n, th);
-        MS::template store<FULL, kNTS>(mom + off, n, zero);
-        if (mom2 != nullptr) store_f32<FULL, kNTS>(mom2 + off, n, zero);
+        PS::template store<F, kNTS>(params + off, n, th);
+        MS::template store<F, kNTS>(mom + off, n, zero);
+        if (mom2 != nullptr) store_f32<F, kNTS>(mom2 + off, n, zero);
     }
-    store_f32<FULL, kNTS>(slow + p0, n, zero);
-    store_f32<FULL, kNTS>(anchor + p0, n, th);
+    store_f32<F, kNTS>(slow + p0, n, zero);
+    store_f32<F, kNTS>(anchor + p0, n, th);
 }
 
 template <class PS, class MS>
@@ -32,11 +32,9 @@ __global__ __launch_bounds__(kBlock) void state_init_kernel(
     float* __restrict__ anchor, int W, int64_t ld, int64_t P) {
     const int64_t p0 = ((int64_t)blockIdx.x * kBlock + threadIdx.x) * kVec;
     if (p0 >= P) return;
-    if (p0 + kVec <= P)
-        init_chunk<PS, MS, true>(theta0, params, mom, mom2, slow, anchor, W, ld, p0, kVec);
-    else
-        init_chunk<PS, MS, false>(theta0, params, mom, mom2, slow, anchor, W, ld, p0,
-                                  (int)(P - p0));
+    for_lanes(p0, P, [&](auto lanes, int n) {
+        init_chunk<PS, MS, lanes>(theta0, params, mom, mom2, slow, anchor, W, ld, p0, n);
+    });
 }
 
 template <Opt O, class PS, class GS, class MS>

@@ -8,16 +8,16 @@ namespace {
 
 // ---- plan initialisation: every replica <- the reference model ----------------
 
-template <class PS, bool FULL>
+template <class PS, int F>
 __device__ __forceinline__ void init_plan_chunk(const float* anchor, typename PS::T* params,
                                                 float* mom, float* mom2, float* slow, int n) {
     float a[kVec];
     const float zero[kVec] = {0.0f, 0.0f, 0.0f, 0.0f};
-    load_f32<FULL, false>(anchor, n, a);
-    PS::template store<FULL, kNTS>(params, n, a);
-    store_f32<FULL, kNTS>(mom, n, zero);
-    if (mom2 != nullptr) store_f32<FULL, kNTS>(mom2, n, zero);
-    if (slow != nullptr) store_f32<FULL, kNTS>(slow, n, zero);
+    load_f32<F, false>(anchor, n, a);
+    PS::template store<F, kNTS>(params, n, a);
+    store_f32<F, kNTS>(mom, n, zero);
+    if (mom2 != nullptr) store_f32<F, kNTS>(mom2, n, zero);
+    if (slow != nullptr) store_f32<F, kNTS>(slow, n, zero);
 }
 
 template <class PS>
@@ -37,10 +37,9 @@ __global__ __launch_bounds__(kBlock) void state_init_plan_kernel(const int64_t* 
     auto* params = reinterpret_cast<typename PS::T*>(v.params[k]) + p0;
     float* mom2 = v.mom2[k] != 0 ? at(v.mom2[k]) : nullptr;
     float* slow = row == 0 && v.slow[t] != 0 ? at(v.slow[t]) : nullptr;
-    if (p0 + kVec <= P)
-        init_plan_chunk<PS, true>(anchor, params, at(v.mom[k]), mom2, slow, kVec);
-    else
-        init_plan_chunk<PS, false>(anchor, params, at(v.mom[k]), mom2, slow, (int)(P - p0));
+    for_lanes(p0, P, [&](auto lanes, int n) {
+        init_plan_chunk<PS, lanes>(anchor, params, at(v.mom[k]), mom2, slow, n);
+    });
 }
 
 }  // namespace

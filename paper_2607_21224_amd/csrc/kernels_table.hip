@@ -35,12 +35,10 @@ __global__ __launch_bounds__(kBlock) void sync_table_kernel(
     StepEntry e;
     if (!step_entry(table, e)) return;
     const Strided<PS> r{params, mom, mom2, const_cast<float*>(grads), ld};
-    if (p0 + kVec <= P)
-        sync_chunk<M, O, 0, PS, true, EXTRA>(e.o, r, slow, anchor, W, p0, kVec, e.beta,
-                                             e.alpha_lr, inv_w, flags);
-    else
-        sync_chunk<M, O, 0, PS, false, EXTRA>(e.o, r, slow, anchor, W, p0, (int)(P - p0),
-                                              e.beta, e.alpha_lr, inv_w, flags);
+    for_lanes(p0, P, [&](auto lanes, int n) {
+        sync_chunk<M, O, 0, PS, lanes, EXTRA>(e.o, r, slow, anchor, W, p0, n, e.beta, e.alpha_lr,
+                                              inv_w, flags);
+    });
 }
 
 // position word updates: one lane of one block, an ordinary (vector) store
