@@ -11,7 +11,9 @@ namespace {
 // of Algorithm 1).  Each thread checks its 4 coordinates over all W replicas,
 // bit for bit (a NaN matches a NaN), the counts are summed across the
 // wavefront with shuffles, and one lane per wavefront adds a nonzero sum to
-// the result with a vector atomic.
+// the result with a vector atomic.  Rows are read in batches of 8, then 4, all
+// of a batch in flight together: one row a time, a wave made W round trips to
+// memory in a row (@CHECK@).
 
 __device__ __forceinline__ bool same_stored(float a, float b) {
     if (a != a && b != b) return true;  // NaN stored as NaN
@@ -22,16 +24,28 @@ template <class PS, int F>
 __device__ __forceinline__ unsigned long long count_chunk(const typename PS::T* params,
                                                           const float* anchor, int W, int64_t ld,
                                                           int64_t p0, int n) {
-    float a[kVec], x[kVec];
+    float a[kVec];
     bool differs[kVec] = {false, false, false, false};
     load_f32<F, false>(anchor + p0, n, a);
 #pragma unroll
     for (int k = 0; k < kVec; ++k) a[k] = PS::round(a[k]);
-    for (int i = 0; i < W; ++i) {
-        PS::template load<F, false>(params + (int64_t)i * ld + p0, n, x);
+    auto batch = [&](auto rows, int i) {
+        float x[rows][kVec];
 #pragma unroll
-        for (int k = 0; k < kVec; ++k) differs[k] = differs[k] || !same_stored(x[k], a[k]);
+        for (int c = 0; c < rows; ++c)
+            PS::template load<F, false>(params + (int64_t)(i + c) * ld + p0, n, x[c]);
+#pragma unroll
+        for (int c = 0; c < rows; ++c)
+#pragma unroll
+            for (int k = 0; k < kVec; ++k) differs[k] |= !same_stored(x[c][k], a[k]);
+    };
+    int i = 0;
+    for (; i + 8 <= W; i += 8) batch(std::integral_constant<int, 8>(), i);
+    if (i + 4 <= W) {
+        batch(std::integral_constant<int, 4>(), i);
+        i += 4;
     }
+    for (; i < W; ++i) batch(std::integral_constant<int, 1>(), i);
     unsigned long long bad = 0;
 #pragma unroll
     for (int k = 0; k < kVec; ++k) bad += (k < n && differs[k]) ? 1u : 0u;
