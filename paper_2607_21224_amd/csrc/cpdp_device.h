@@ -318,13 +318,21 @@ __device__ __forceinline__ PlanView plan_view(const int64_t* plan, int64_t W, in
 }
 
 // tensor holding chunk b: the largest t < n with chunk_start[t] <= b (an
-// empty tensor never qualifies as the last such t, since b < chunk_start[n])
-__device__ __forceinline__ int64_t plan_tensor(const PlanView& v, int64_t n, int64_t b) {
-    int64_t lo = 0, hi = n;
+// empty tensor never qualifies as the last such t, since b < chunk_start[n]).
+// Called by whole wavefronts: the 64 lanes look at 64 evenly spaced starts at
+// once, so 161 tensors take two dependent loads where a binary search by every
+// thread took eight, each a trip to L2 or beyond before the first data load
+// could be issued (AdamW local step of 4 x 271,117 coordinates in 62 tensors:
+// @LOCAL@).
+__device__ __forceinline__ int64_t plan_tensor(const PlanView& v, int n, int64_t b) {
+    const int lane = (int)(threadIdx.x % 64);
+    int lo = 0, hi = n;  // chunk_start[lo] <= b < chunk_start[hi]
     while (hi - lo > 1) {
-        const int64_t mid = (lo + hi) >> 1;
-        if (v.chunk_start[mid] <= b) lo = mid;
-        else hi = mid;
+        const int step = (hi - lo + 63) / 64;
+        const int at = lo + lane * step;
+        const bool le = at < hi && v.chunk_start[at] <= b;
+        lo += (__popcll(__ballot(le)) - 1) * step;  // starts do not decrease: a prefix of lanes
+        hi = min(hi, lo + step);
     }
     return lo;
 }
@@ -347,10 +355,59 @@ __device__ __forceinline__ int64_t local_cell(int64_t cells) {
     return (int64_t)blockIdx.x < cells ? (int64_t)blockIdx.x : -1;
 }
 
+// ---- step tables: the scalars of the current step read from device memory -----
+//
+// Every thread reads the position word and that entry (the same addresses for
+// the whole grid, so they are served from cache).  A position outside the
+// table means the table is used up: the kernel returns without touching the
+// state, so replaying a captured graph past its table cannot run a step with
+// undefined scalars.
+
+// The table does not change while a step runs, so it is read through the
+// constant address space (scalar loads, which do not wait for the data).
+__device__ __forceinline__ bool step_entry(const int64_t* table, StepEntry& e) {
+    typedef const int64_t __attribute__((address_space(4))) Word;
+    typedef const StepEntry __attribute__((address_space(4))) Entry;
+    Word* t = (Word*)table;
+    const int64_t pos = t[0], n = t[1];
+    if ((uint64_t)pos >= (uint64_t)n) return false;
+    Entry* at = (Entry*)(t + kStepTableHeaderWords) + pos;
+    e.o = {at->o.lr, at->o.mu, at->o.wd, at->o.omb1, at->o.beta2,
+           at->o.omb2, at->o.eps, at->o.step_size, at->o.sqrt_bc2, at->o.decay};
+    e.beta = at->beta;
+    e.alpha_lr = at->alpha_lr;
+    return true;
+}
+
+// Keeps the loads written before it ahead of what follows: the compiler would
+// move them past the test of a table's position, behind its two dependent loads.
+__device__ __forceinline__ void loads_first() { asm volatile("" ::: "memory"); }
+
+// Where a step's scalars come from: the launch arguments, or the entry at the
+// position of a device step table (no entry when the table is used up).
+struct DirectScalars {
+    static constexpr bool kDeferred = false;
+    OptParams o;
+    float beta;
+    float alpha_lr;
+    __device__ __forceinline__ bool get(StepEntry& e) const {
+        e.o = o;
+        e.beta = beta;
+        e.alpha_lr = alpha_lr;
+        return true;
+    }
+};
+
+struct TableScalars {
+    static constexpr bool kDeferred = true;
+    const int64_t* table;
+    __device__ __forceinline__ bool get(StepEntry& e) const { return step_entry(table, e); }
+};
+
 // ---- local step: one replica row per block, 4 coordinates per thread -------
 
-template <Opt O, class PS, class GS, class MS, int F>
-__device__ __forceinline__ void local_chunk(const OptParams& o, typename PS::T* params,
+template <Opt O, class PS, class GS, class MS, int F, class Src>
+__device__ __forceinline__ void local_chunk(const Src& src, typename PS::T* params,
                                             typename MS::T* mom, float* mom2,
                                             const typename GS::T* grads, int n) {
     float g[kVec], m[kVec], v[kVec] = {0.0f, 0.0f, 0.0f, 0.0f}, th[kVec];
@@ -358,20 +415,24 @@ __device__ __forceinline__ void local_chunk(const OptParams& o, typename PS::T* 
     MS::template load<F, kNTL>(mom, n, m);
     if constexpr (O == Opt::ADAMW) load_f32<F, kNTL>(mom2, n, v);
     PS::template load<F, kNTL>(params, n, th);
+    // a table's entry is two dependent loads away: look while the data comes
+    if constexpr (Src::kDeferred) loads_first();
+    StepEntry e;
+    if (!src.get(e)) return;
 #pragma unroll
-    for (int k = 0; k < kVec; ++k) th[k] = opt_update<O, PS, MS>(o, th[k], m[k], v[k], g[k]);
+    for (int k = 0; k < kVec; ++k) th[k] = opt_update<O, PS, MS>(e.o, th[k], m[k], v[k], g[k]);
     MS::template store<F, kNTS>(mom, n, m);
     if constexpr (O == Opt::ADAMW) store_f32<F, kNTS>(mom2, n, v);
     PS::template store<F, kNTS>(params, n, th);
 }
 
-template <Opt O, class PS, class GS = ParamF32, class MS = ParamF32>
-__device__ __forceinline__ void local_dispatch(const OptParams& o, typename PS::T* params,
+template <Opt O, class PS, class GS = ParamF32, class MS = ParamF32, class Src>
+__device__ __forceinline__ void local_dispatch(const Src& src, typename PS::T* params,
                                                typename MS::T* mom, float* mom2,
                                                const typename GS::T* grads, int64_t p0,
                                                int64_t P) {
     for_lanes(p0, P, [&](auto lanes, int n) {
-        local_chunk<O, PS, GS, MS, lanes>(o, params + p0, mom + p0, mom2 + p0, grads + p0, n);
+        local_chunk<O, PS, GS, MS, lanes>(src, params + p0, mom + p0, mom2 + p0, grads + p0, n);
     });
 }
 
@@ -558,40 +619,6 @@ __device__ __forceinline__ void sync_chunk(const OptParams& o, const Rows& r, fl
 // write-back), so only those instantiations take them as mutable.
 template <bool EXTRA, class GS = ParamF32>
 using GradPtr = typename std::conditional<EXTRA, typename GS::T*, const typename GS::T*>::type;
-
-// ---- step tables: the scalars of the current step read from device memory -----
-//
-// Every thread reads the position word and that entry (the same addresses for
-// the whole grid, so they are served from cache).  A position outside the
-// table means the table is used up: the kernel returns without touching the
-// state, so replaying a captured graph past its table cannot run a step with
-// undefined scalars.
-
-__device__ __forceinline__ bool step_entry(const int64_t* table, StepEntry& e) {
-    const int64_t pos = table[0];
-    if (pos < 0 || pos >= table[1]) return false;
-    e = reinterpret_cast<const StepEntry*>(table + kStepTableHeaderWords)[pos];
-    return true;
-}
-
-// Where a step's scalars come from: the launch arguments, or the entry at the
-// position of a device step table (no entry when the table is used up).
-struct DirectScalars {
-    OptParams o;
-    float beta;
-    float alpha_lr;
-    __device__ __forceinline__ bool get(StepEntry& e) const {
-        e.o = o;
-        e.beta = beta;
-        e.alpha_lr = alpha_lr;
-        return true;
-    }
-};
-
-struct TableScalars {
-    const int64_t* table;
-    __device__ __forceinline__ bool get(StepEntry& e) const { return step_entry(table, e); }
-};
 
 // ---- launch helpers -------------------------------------------------------------
 

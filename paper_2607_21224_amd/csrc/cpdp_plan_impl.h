@@ -4,7 +4,7 @@
 // and kernels_plan_table.hip instantiate one source each.
 #pragma once
 
-#include "cpdp_device.h"
+#include "cpdp_split.h"
 
 namespace cpdp {
 namespace {
@@ -25,11 +25,9 @@ __global__ __launch_bounds__(kBlock) void local_step_plan_kernel(Src src,
     const int64_t P = v.numel[t];
     const int64_t p0 = ((b - v.chunk_start[t]) * kBlock + threadIdx.x) * kVec;
     if (p0 >= P) return;
-    StepEntry e;
-    if (!src.get(e)) return;
     const Table<PS> r{v.params, v.mom, v.mom2, v.grads, n, t};
     const int i = (int)row;
-    local_dispatch<O, PS>(e.o, r.prm(i), r.m(i), O == Opt::ADAMW ? r.v(i) : nullptr, r.g(i), p0,
+    local_dispatch<O, PS>(src, r.prm(i), r.m(i), O == Opt::ADAMW ? r.v(i) : nullptr, r.g(i), p0,
                           P);
 }
 
@@ -53,6 +51,23 @@ __global__ __launch_bounds__(kBlock) void sync_plan_kernel(Src src,
         sync_chunk<M, O, 0, PS, lanes, EXTRA>(e.o, r, slow, anchor, W, p0, n, e.beta, e.alpha_lr,
                                               inv_w, flags);
     });
+}
+
+// the split step over chunk b's tensor (reconcile of the 4 x 271,117 AdamW
+// state in 62 tensors: @SYNC@; 8 x 23.7 M, 161 tensors, weight decay:
+// @BIG@)
+template <Sync M, Opt O, int R, class PS, bool EXTRA, class Src>
+__global__ __launch_bounds__(kSplitThreads) void sync_plan_split_kernel(
+    Src src, const int64_t* __restrict__ plan, int W, int n, float inv_w, unsigned flags) {
+    extern __shared__ __align__(16) float lds[];
+    const PlanView v = plan_view(plan, W, n);
+    const int64_t b = blockIdx.x;
+    const int64_t t = plan_tensor(v, n, b);
+    const Table<PS> r{v.params, v.mom, v.mom2, v.grads, n, t};
+    split_dispatch<M, O, R, PS, EXTRA>(src, r, reinterpret_cast<float*>(v.slow[t]),
+                                       reinterpret_cast<float*>(v.anchor[t]), W,
+                                       (b - v.chunk_start[t]) * kCoords, v.numel[t], inv_w, flags,
+                                       lds);
 }
 
 template <Opt O, class Src>
@@ -79,6 +94,15 @@ template <Sync M, Opt O, class PS, class Src>
 int sync_plan_t(Src src, const int64_t* plan, int W, int n, int64_t total_chunks,
                 unsigned flags, void* stream) {
     const float inv_w = 1.0f / (float)W;
+    if (can_split(W))
+        return with_split_r<PS>(W, [&](auto R) {
+            return flags != 0 ? launch_split(sync_plan_split_kernel<M, O, R, PS, true, Src>,
+                                             total_chunks, W, R, stream, src, plan, W, n, inv_w,
+                                             flags)
+                              : launch_split(sync_plan_split_kernel<M, O, R, PS, false, Src>,
+                                             total_chunks, W, R, stream, src, plan, W, n, inv_w,
+                                             flags);
+        });
     if (flags != 0)
         return launch(sync_plan_kernel<M, O, PS, true, Src>, total_chunks, stream, src, plan, W,
                       n, inv_w, flags);

@@ -107,6 +107,7 @@ __device__ __forceinline__ void split_chunk(const Src& src, const Rows& r, float
             load_f32<F, kNTL>(slow + p0, n, u);
         }
     }
+    if constexpr (Src::kDeferred) loads_first();
     StepEntry e;
     if (!src.get(e)) return;  // the same for the whole grid
 

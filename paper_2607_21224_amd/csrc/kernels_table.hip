@@ -1,14 +1,13 @@
 // Step tables: the local and synchronisation steps with their scalars read
 // from a device table, and the kernels that move the table's position.
-#include "cpdp_device.h"
+#include "cpdp_split.h"
 
 namespace cpdp {
 namespace {
 
 template <Opt O, class PS>
 __global__ __launch_bounds__(kBlock) void local_step_table_kernel(
-    const int64_t* __restrict__ table, typename PS::T* __restrict__ params,
-    float* __restrict__ mom, float* __restrict__ mom2, const float* __restrict__ grads,
+    const int64_t* table, typename PS::T* params, float* mom, float* mom2, const float* grads,
     int64_t ld, int64_t P, int64_t blocks_per_row, int64_t cells) {
     const int64_t cell = local_cell(cells);
     if (cell < 0) return;
@@ -16,10 +15,8 @@ __global__ __launch_bounds__(kBlock) void local_step_table_kernel(
     const int64_t col = cell - row * blocks_per_row;
     const int64_t p0 = (col * kBlock + threadIdx.x) * kVec;
     if (p0 >= P) return;
-    StepEntry e;
-    if (!step_entry(table, e)) return;
     const int64_t off = row * ld;
-    local_dispatch<O, PS>(e.o, params + off, mom + off, mom2 + off, grads + off, p0, P);
+    local_dispatch<O, PS>(TableScalars{table}, params + off, mom + off, mom2 + off, grads + off, p0, P);
 }
 
 // run-time W (replica batches of kChunk): one instantiation per strategy,
@@ -69,6 +66,11 @@ template <Sync M, Opt O, class PS>
 int sync_table_t(const int64_t* table, const SyncArgs& a) {
     using T = typename PS::T;
     const float inv_w = 1.0f / (float)a.W;
+    if (can_split(a.W)) {
+        const TableScalars src{table};
+        return a.flags != 0 ? sync_split<M, O, PS, true, ParamF32, ParamF32>(src, a)
+                            : sync_split<M, O, PS, false, ParamF32, ParamF32>(src, a);
+    }
     // step tables take fp32 gradients
     const float* grads = static_cast<const float*>(a.grads);
     if (a.flags != 0)
