@@ -397,6 +397,31 @@ int cpdp_sync_step_table(int strategy, void* params, void* mom, void* mom2,
                          int64_t P, int64_t ld, int K, const cpdp_step_table* t,
                          unsigned flags, int param_dt, void* stream);
 
+/* For a run of table steps that is enqueued as a whole, as a captured period
+ * is: the same steps without an advance kernel after each.
+ *   cpdp_local_steps_table   n_steps (1 to 8) consecutive local steps in one
+ *       launch, step j with the gradient rows grads[j] (a host array of device
+ *       addresses, each [W x ld] fp32) and the entry ahead + j places past the
+ *       position.  The state is bitwise that of n_steps cpdp_local_step_table
+ *       calls with an advance after each; steps past the table's end change
+ *       nothing.  NULL grads: CPDP_ERR_NULL.
+ *   cpdp_sync_step_table_ahead   cpdp_sync_step_table with the entry `ahead`
+ *       places past the position.
+ *   cpdp_step_table_advance_by   `steps` advances in one kernel.
+ * ahead outside [0, n_steps of the table], steps < 0 or n_steps outside its
+ * range: CPDP_ERR_INVALID_ARG. */
+int cpdp_local_steps_table(void* params, void* mom, void* mom2,
+                           const void* const* grads, int n_steps, int W, int64_t P,
+                           int64_t ld, int K, const cpdp_step_table* t, int64_t ahead,
+                           int param_dt, void* stream);
+int cpdp_sync_step_table_ahead(int strategy, void* params, void* mom, void* mom2,
+                               void* grads, float* slow_mom, float* anchor, int W,
+                               int64_t P, int64_t ld, int K,
+                               const cpdp_step_table* t, int64_t ahead,
+                               unsigned flags, int param_dt, void* stream);
+int cpdp_step_table_advance_by(const cpdp_step_table* t, int64_t steps,
+                               void* stream);
+
 /* cpdp_local_step_plan / cpdp_sync_step_plan with the scalars (and beta,
  * alpha) of a step table's current entry; the update rule is the table's.
  * An AdamW table needs a plan with mom2.  Do not advance the position. */

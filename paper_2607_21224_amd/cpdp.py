@@ -42,7 +42,9 @@ EXPORTS = ("cpdp_state_init", "cpdp_local_step", "cpdp_reconcile",
            "cpdp_state_init_plan", "cpdp_local_step_plan", "cpdp_sync_step_plan",
            "cpdp_step_table_bytes", "cpdp_step_table_fill", "cpdp_step_table_set_position",
            "cpdp_step_table_advance", "cpdp_step_table_position", "cpdp_local_step_table",
-           "cpdp_sync_step_table", "cpdp_local_step_plan_table", "cpdp_sync_step_plan_table",
+           "cpdp_sync_step_table", "cpdp_local_steps_table", "cpdp_sync_step_table_ahead",
+           "cpdp_step_table_advance_by", "cpdp_local_step_plan_table",
+           "cpdp_sync_step_plan_table",
            "cpdp_count_unsynced", "cpdp_status_str")
 
 CPDP_OPT_SGD = 0
@@ -136,6 +138,14 @@ def load_library(path: str = LIB_PATH) -> ctypes.CDLL:
     for name in ("cpdp_step_table_fill", "cpdp_step_table_set_position",
                  "cpdp_step_table_advance", "cpdp_step_table_position",
                  "cpdp_local_step_table", "cpdp_sync_step_table"):
+        getattr(lib, name).restype = i
+    lib.cpdp_local_steps_table.argtypes = [vp, vp, vp, ctypes.POINTER(vp), i, i, i64, i64, i, tp,
+                                           i64, i, vp]
+    lib.cpdp_sync_step_table_ahead.argtypes = [i, vp, vp, vp, vp, vp, vp, i, i64, i64, i, tp, i64,
+                                               ctypes.c_uint, i, vp]
+    lib.cpdp_step_table_advance_by.argtypes = [tp, i64, vp]
+    for name in ("cpdp_local_steps_table", "cpdp_sync_step_table_ahead",
+                 "cpdp_step_table_advance_by"):
         getattr(lib, name).restype = i
     lib.cpdp_local_step_plan_table.argtypes = [pp, i, tp, vp]
     lib.cpdp_local_step_plan_table.restype = i
@@ -531,6 +541,39 @@ def cpdp_sync_step_table(strategy, params, mom, mom2, grads, slow_mom, anchor, W
                                  int(ld), int(K), ctypes.byref(t), int(flags), _dt(param_dt),
                                  _stream(stream))
     return _done(s, "cpdp_sync_step_table", check)
+
+
+def cpdp_local_steps_table(params, mom, mom2, grads, W, P, ld, K, t: cpdp_step_table, ahead=0,
+                           param_dt=CPDP_F32, stream=None, check=True):
+    """Consecutive local steps in one launch; grads: one tensor or address a
+    step (1 to 8)."""
+    arr = (ctypes.c_void_p * len(grads))(*[_rows(g, W, P, ld, CPDP_F32, f"grads[{j}]")
+                                           for j, g in enumerate(grads)])
+    s = lib.cpdp_local_steps_table(_rows(params, W, P, ld, param_dt, "params"),
+                                   _rows(mom, W, P, ld, CPDP_F32, "mom"),
+                                   _rows(mom2, W, P, ld, CPDP_F32, "mom2"), arr, len(grads),
+                                   int(W), int(P), int(ld), int(K), ctypes.byref(t), int(ahead),
+                                   _dt(param_dt), _stream(stream))
+    return _done(s, "cpdp_local_steps_table", check)
+
+
+def cpdp_sync_step_table_ahead(strategy, params, mom, mom2, grads, slow_mom, anchor, W, P, ld, K,
+                               t: cpdp_step_table, ahead=0, flags=0, param_dt=CPDP_F32,
+                               stream=None, check=True):
+    strategy = SYNC_KINDS[strategy] if isinstance(strategy, str) else int(strategy)
+    s = lib.cpdp_sync_step_table_ahead(strategy, _rows(params, W, P, ld, param_dt, "params"),
+                                       _rows(mom, W, P, ld, CPDP_F32, "mom"),
+                                       _rows(mom2, W, P, ld, CPDP_F32, "mom2"),
+                                       _rows(grads, W, P, ld, CPDP_F32, "grads"),
+                                       _vec(slow_mom, P, "slow_mom"), _vec(anchor, P, "anchor"),
+                                       int(W), int(P), int(ld), int(K), ctypes.byref(t),
+                                       int(ahead), int(flags), _dt(param_dt), _stream(stream))
+    return _done(s, "cpdp_sync_step_table_ahead", check)
+
+
+def cpdp_step_table_advance_by(t: cpdp_step_table, steps: int, stream=None, check=True):
+    return _done(lib.cpdp_step_table_advance_by(ctypes.byref(t), int(steps), _stream(stream)),
+                 "cpdp_step_table_advance_by", check)
 
 
 def cpdp_count_unsynced(params, anchor, W, P, ld, count, param_dt=CPDP_F32, stream=None,

@@ -734,6 +734,31 @@ int cpdp_local_step_table(void* params, void* mom, void* mom2, const void* grads
         static_cast<const float*>(grads), W, P, ld, stream));
 }
 
+int cpdp_local_steps_table(void* params, void* mom, void* mom2, const void* const* grads,
+                           int n_steps, int W, int64_t P, int64_t ld, int K,
+                           const cpdp_step_table* t, int64_t ahead, int param_dt, void* stream) {
+    if (int s = check_shape(W, P, ld, K)) return s;
+    if (n_steps < 1 || n_steps > cpdp::kMaxLocalSteps || ahead < 0) return CPDP_ERR_INVALID_ARG;
+    if (grads == nullptr) return CPDP_ERR_NULL;
+    cpdp::Opt kind;
+    if (int s = check_step_table(t, &kind)) return s;
+    if (ahead > t->n_steps) return CPDP_ERR_INVALID_ARG;
+    if (!is_dtype(param_dt)) return CPDP_ERR_DTYPE;
+    if (P == 0) return CPDP_OK;
+    if (!cpdp::grid_fits(W, P)) return CPDP_ERR_INVALID_ARG;
+    const bool adam = kind == cpdp::Opt::ADAMW;
+    const float* rows[cpdp::kMaxLocalSteps];
+    for (int j = 0; j < n_steps; ++j) {
+        if (int s = check_local_ptrs(params, mom, mom2, grads[j], W, P, ld, esize(param_dt), adam))
+            return s;
+        rows[j] = static_cast<const float*>(grads[j]);
+    }
+    return hip_status(cpdp::launch_local_steps_table(
+        kind, param_kind(param_dt), static_cast<const int64_t*>(t->table), ahead, params,
+        static_cast<float*>(mom), adam ? static_cast<float*>(mom2) : nullptr, rows, n_steps, W, P,
+        ld, stream));
+}
+
 int cpdp_sync_step_table(int strategy, void* params, void* mom, void* mom2, void* grads,
                          float* slow_mom, float* anchor, int W, int64_t P, int64_t ld, int K,
                          const cpdp_step_table* t, unsigned flags, int param_dt, void* stream) {
@@ -755,6 +780,39 @@ int cpdp_sync_step_table(int strategy, void* params, void* mom, void* mom2, void
         sync_mode(strategy), kind, param_kind(param_dt), static_cast<const int64_t*>(t->table),
         params, static_cast<float*>(mom), static_cast<float*>(m2),
         static_cast<const float*>(grads), slow, anc, W, P, ld, flags, stream));
+}
+
+int cpdp_sync_step_table_ahead(int strategy, void* params, void* mom, void* mom2, void* grads,
+                         float* slow_mom, float* anchor, int W, int64_t P, int64_t ld, int K,
+                         const cpdp_step_table* t, int64_t ahead, unsigned flags,
+                               int param_dt, void* stream) {
+    if (int s = check_shape(W, P, ld, K)) return s;
+    if (flags & ~kKnownFlags) return CPDP_ERR_INVALID_ARG;
+    if (!valid_strategy(strategy)) return CPDP_ERR_INVALID_ARG;
+    cpdp::Opt kind;
+    if (int s = check_step_table(t, &kind)) return s;
+    if (ahead < 0 || ahead > t->n_steps) return CPDP_ERR_INVALID_ARG;
+    if (!is_dtype(param_dt)) return CPDP_ERR_DTYPE;
+    if (P == 0) return CPDP_OK;
+    if (!cpdp::grid_fits(1, P)) return CPDP_ERR_INVALID_ARG;
+    float* slow;
+    float* anc;
+    void* m2;
+    if (int s = check_sync_ptrs(strategy, kind == cpdp::Opt::ADAMW, params, mom, mom2, grads,
+                                slow_mom, anchor, W, P, ld, esize(param_dt), &slow, &anc, &m2))
+        return s;
+    return hip_status(cpdp::launch_sync_table_ahead(
+        sync_mode(strategy), kind, param_kind(param_dt), static_cast<const int64_t*>(t->table),
+        ahead, params, static_cast<float*>(mom), static_cast<float*>(m2),
+        static_cast<const float*>(grads), slow, anc, W, P, ld, flags, stream));
+}
+
+int cpdp_step_table_advance_by(const cpdp_step_table* t, int64_t steps, void* stream) {
+    cpdp::Opt kind;
+    if (int s = check_step_table(t, &kind)) return s;
+    if (steps < 0) return CPDP_ERR_INVALID_ARG;
+    return hip_status(
+        cpdp::launch_step_table_advance_by(static_cast<int64_t*>(t->table), steps, stream));
 }
 
 int cpdp_local_step_plan_table(const cpdp_plan* plan, int K, const cpdp_step_table* t,

@@ -8,14 +8,16 @@
 // instantiates only what it launches.
 //
 // All of them are HBM-streaming kernels: nothing here is a dense contraction, so
-// there is no MFMA and no LDS.  Every thread owns VEC = 4 consecutive
-// coordinates and moves them with 128-bit (fp32) or 64-bit (bf16) vector
-// accesses (parameters, and on the plain momentum-SGD entry points also the
-// gradients and the momentum, may be stored as bf16); a wavefront therefore touches 1 KiB (fp32) of each array row per
-// access, fully coalesced.  Every output element is written by exactly one
-// thread, there are no atomics and no inter-block dependencies, and the
-// cross-replica sums run in a fixed order (replica 0, 1, ..., W-1) inside one
-// thread, so results are bitwise independent of the launch shape.
+// there is no MFMA.  Every thread owns VEC = 4 consecutive coordinates and moves
+// them with 128-bit (fp32) or 64-bit (bf16) vector accesses (parameters, and on
+// the plain momentum-SGD entry points also the gradients and the momentum, may
+// be stored as bf16); a wavefront therefore touches 1 KiB (fp32) of each array
+// row per access, fully coalesced.  Every output element is written by exactly
+// one thread, there are no atomics and no inter-block dependencies, and the
+// cross-replica sums run in a fixed order (replica 0, 1, ..., W-1), whether one
+// thread holds a coordinate of all replicas (sync_chunk) or a block's wavefronts
+// hold one each and meet in LDS (split_chunk), so results are bitwise
+// independent of the launch shape.
 //
 // Arithmetic is fp32 with explicit fmaf in the optimizer updates and the
 // SlowMo step (the library is built with -ffp-contract=off so nothing else is
@@ -112,7 +114,7 @@ __device__ __forceinline__ void load_f32(const float* p, int n, float (&x)[kVec]
         f32x4 v = vload<NT>(reinterpret_cast<const f32x4*>(p));
         x[0] = v.x; x[1] = v.y; x[2] = v.z; x[3] = v.w;
     } else if constexpr (F == kRagged) {
-        const f32x4_el v = vload<NT>(reinterpret_cast<const f32x4_el*>(p - (kVec - n)));
+        const f32x4_el v = *reinterpret_cast<const f32x4_el*>(p - (kVec - n));
         x[0] = v.x; x[1] = v.y; x[2] = v.z; x[3] = v.w;
         shift_down(kVec - n, x);
     } else {
@@ -179,7 +181,7 @@ struct ParamBF16 {
             if constexpr (F == kFull)
                 v = vload<NT>(reinterpret_cast<const u32x2*>(p));
             else
-                v = vload<NT>(reinterpret_cast<const u32x2_el*>(p - (kVec - n)));
+                v = *reinterpret_cast<const u32x2_el*>(p - (kVec - n));
             x[0] = __uint_as_float(v.x << 16);
             x[1] = __uint_as_float(v.x & 0xFFFF0000u);
             x[2] = __uint_as_float(v.y << 16);
@@ -275,6 +277,14 @@ struct Strided {
     __device__ __forceinline__ typename GS::T* g(int i) const { return grads + (int64_t)i * ld; }
 };
 
+// An address from a plan table as a pointer to global memory.  A plain cast of
+// the integer makes a generic pointer, whose flat accesses also wait on the LDS
+// counter.
+template <class T>
+__device__ __forceinline__ T* global_ptr(int64_t addr) {
+    return (T*)(T __attribute__((address_space(1)))*)addr;
+}
+
 template <class PS>
 struct Table {
     using GS = ParamF32;    // plans hold fp32 gradients
@@ -285,11 +295,11 @@ struct Table {
     const int64_t* grads;
     int64_t n, t;
     __device__ __forceinline__ typename PS::T* prm(int i) const {
-        return reinterpret_cast<typename PS::T*>(params[i * n + t]);
+        return global_ptr<typename PS::T>(params[i * n + t]);
     }
-    __device__ __forceinline__ float* m(int i) const { return reinterpret_cast<float*>(mom[i * n + t]); }
-    __device__ __forceinline__ float* v(int i) const { return reinterpret_cast<float*>(mom2[i * n + t]); }
-    __device__ __forceinline__ float* g(int i) const { return reinterpret_cast<float*>(grads[i * n + t]); }
+    __device__ __forceinline__ float* m(int i) const { return global_ptr<float>(mom[i * n + t]); }
+    __device__ __forceinline__ float* v(int i) const { return global_ptr<float>(mom2[i * n + t]); }
+    __device__ __forceinline__ float* g(int i) const { return global_ptr<float>(grads[i * n + t]); }
 };
 
 // The sections of a plan table (layout documented in cpdp_launch.h).
@@ -322,8 +332,8 @@ __device__ __forceinline__ PlanView plan_view(const int64_t* plan, int64_t W, in
 // Called by whole wavefronts: the 64 lanes look at 64 evenly spaced starts at
 // once, so 161 tensors take two dependent loads where a binary search by every
 // thread took eight, each a trip to L2 or beyond before the first data load
-// could be issued (AdamW local step of 4 x 271,117 coordinates in 62 tensors:
-// @LOCAL@).
+// could be issued (AdamW reconcile of 4 x 271,117 coordinates in 62
+// tensors, with the split step: 14.0 -> 8.3 us).
 __device__ __forceinline__ int64_t plan_tensor(const PlanView& v, int n, int64_t b) {
     const int lane = (int)(threadIdx.x % 64);
     int lo = 0, hi = n;  // chunk_start[lo] <= b < chunk_start[hi]
@@ -357,7 +367,7 @@ __device__ __forceinline__ int64_t local_cell(int64_t cells) {
 
 // ---- step tables: the scalars of the current step read from device memory -----
 //
-// Every thread reads the position word and that entry (the same addresses for
+// Every thread reads the position word and the entry `ahead` places past it (the same addresses for
 // the whole grid, so they are served from cache).  A position outside the
 // table means the table is used up: the kernel returns without touching the
 // state, so replaying a captured graph past its table cannot run a step with
@@ -365,11 +375,12 @@ __device__ __forceinline__ int64_t local_cell(int64_t cells) {
 
 // The table does not change while a step runs, so it is read through the
 // constant address space (scalar loads, which do not wait for the data).
-__device__ __forceinline__ bool step_entry(const int64_t* table, StepEntry& e) {
+__device__ __forceinline__ bool step_entry(const int64_t* table, int64_t ahead,
+                                           StepEntry& e) {
     typedef const int64_t __attribute__((address_space(4))) Word;
     typedef const StepEntry __attribute__((address_space(4))) Entry;
     Word* t = (Word*)table;
-    const int64_t pos = t[0], n = t[1];
+    const int64_t pos = t[0] + ahead, n = t[1];
     if ((uint64_t)pos >= (uint64_t)n) return false;
     Entry* at = (Entry*)(t + kStepTableHeaderWords) + pos;
     e.o = {at->o.lr, at->o.mu, at->o.wd, at->o.omb1, at->o.beta2,
@@ -401,7 +412,8 @@ struct DirectScalars {
 struct TableScalars {
     static constexpr bool kDeferred = true;
     const int64_t* table;
-    __device__ __forceinline__ bool get(StepEntry& e) const { return step_entry(table, e); }
+    int64_t ahead;  // entries past the position
+    __device__ __forceinline__ bool get(StepEntry& e) const { return step_entry(table, ahead, e); }
 };
 
 // ---- local step: one replica row per block, 4 coordinates per thread -------

@@ -117,6 +117,24 @@ int launch_sync_table(Sync mode, Opt opt, Param pt, const int64_t* table, void* 
                       float* mom, float* mom2, const float* grads, float* slow, float* anchor,
                       int W, int64_t P, int64_t ld, unsigned flags, void* stream);
 
+// What a captured run of table steps uses: J consecutive local steps in one
+// launch, a synchronisation step, both with the entries `ahead` places past the
+// position, and an advance over all of them.  Weak, so that a host-only build
+// of the validation layer may do without them.
+constexpr int kMaxLocalSteps = 8;
+__attribute__((weak)) int launch_local_steps_table(Opt opt, Param pt, const int64_t* table,
+                                                   int64_t ahead, void* params, float* mom,
+                                                   float* mom2, const float* const* grads, int J,
+                                                   int W, int64_t P, int64_t ld, void* stream);
+__attribute__((weak)) int launch_sync_table_ahead(Sync mode, Opt opt, Param pt,
+                                                  const int64_t* table, int64_t ahead,
+                                                  void* params, float* mom, float* mom2,
+                                                  const float* grads, float* slow, float* anchor,
+                                                  int W, int64_t P, int64_t ld, unsigned flags,
+                                                  void* stream);
+__attribute__((weak)) int launch_step_table_advance_by(int64_t* table, int64_t steps,
+                                                       void* stream);
+
 // Plan steps with the scalars of a step table's current entry.
 int launch_local_step_plan_table(Opt opt, Param pt, const int64_t* plan, int W, int n,
                                  int64_t total_chunks, const int64_t* table, void* stream);

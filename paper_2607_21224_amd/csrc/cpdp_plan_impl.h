@@ -22,13 +22,16 @@ __global__ __launch_bounds__(kBlock) void local_step_plan_kernel(Src src,
     const int64_t row = cell / total_chunks;
     const int64_t b = cell - row * total_chunks;
     const int64_t t = plan_tensor(v, n, b);
-    const int64_t P = v.numel[t];
-    const int64_t p0 = ((b - v.chunk_start[t]) * kBlock + threadIdx.x) * kVec;
+    // the tensor's size and its four addresses come in one round trip: behind
+    // the test of p0 the addresses would take a second one
+    const int64_t k = row * n + t;
+    int64_t P = v.numel[t], start = v.chunk_start[t];
+    int64_t prm = v.params[k], m = v.mom[k], m2 = v.mom2[k], g = v.grads[k];
+    asm volatile("" : "+s"(P), "+s"(start), "+s"(prm), "+s"(m), "+s"(m2), "+s"(g));
+    const int64_t p0 = ((b - start) * kBlock + threadIdx.x) * kVec;
     if (p0 >= P) return;
-    const Table<PS> r{v.params, v.mom, v.mom2, v.grads, n, t};
-    const int i = (int)row;
-    local_dispatch<O, PS>(src, r.prm(i), r.m(i), O == Opt::ADAMW ? r.v(i) : nullptr, r.g(i), p0,
-                          P);
+    local_dispatch<O, PS>(src, global_ptr<typename PS::T>(prm), global_ptr<float>(m),
+                          global_ptr<float>(m2), global_ptr<const float>(g), p0, P);
 }
 
 // block b -> tensor t and its chunk; run-time W
@@ -45,17 +48,17 @@ __global__ __launch_bounds__(kBlock) void sync_plan_kernel(Src src,
     StepEntry e;
     if (!src.get(e)) return;
     const Table<PS> r{v.params, v.mom, v.mom2, v.grads, n, t};
-    float* slow = reinterpret_cast<float*>(v.slow[t]);
-    float* anchor = reinterpret_cast<float*>(v.anchor[t]);
+    float* slow = global_ptr<float>(v.slow[t]);
+    float* anchor = global_ptr<float>(v.anchor[t]);
     for_lanes(p0, P, [&](auto lanes, int n) {
         sync_chunk<M, O, 0, PS, lanes, EXTRA>(e.o, r, slow, anchor, W, p0, n, e.beta, e.alpha_lr,
                                               inv_w, flags);
     });
 }
 
-// the split step over chunk b's tensor (reconcile of the 4 x 271,117 AdamW
-// state in 62 tensors: @SYNC@; 8 x 23.7 M, 161 tensors, weight decay:
-// @BIG@)
+// the split step over chunk b's tensor, for every W it takes (AdamW reconcile of
+// 4 x 271,117 coordinates in 62 tensors: 14.0 -> 8.3 us; weight decay, 8 x 23.7 M
+// in 161 tensors: 764 -> 726 us, 5.8 TB/s)
 template <Sync M, Opt O, int R, class PS, bool EXTRA, class Src>
 __global__ __launch_bounds__(kSplitThreads) void sync_plan_split_kernel(
     Src src, const int64_t* __restrict__ plan, int W, int n, float inv_w, unsigned flags) {
@@ -64,8 +67,8 @@ __global__ __launch_bounds__(kSplitThreads) void sync_plan_split_kernel(
     const int64_t b = blockIdx.x;
     const int64_t t = plan_tensor(v, n, b);
     const Table<PS> r{v.params, v.mom, v.mom2, v.grads, n, t};
-    split_dispatch<M, O, R, PS, EXTRA>(src, r, reinterpret_cast<float*>(v.slow[t]),
-                                       reinterpret_cast<float*>(v.anchor[t]), W,
+    split_dispatch<M, O, R, PS, EXTRA>(src, r, global_ptr<float>(v.slow[t]),
+                                       global_ptr<float>(v.anchor[t]), W,
                                        (b - v.chunk_start[t]) * kCoords, v.numel[t], inv_w, flags,
                                        lds);
 }

@@ -32,9 +32,9 @@ __global__ __launch_bounds__(kBlock) void state_init_plan_kernel(const int64_t* 
     const int64_t p0 = ((b - v.chunk_start[t]) * kBlock + threadIdx.x) * kVec;
     if (p0 >= P) return;
     const int64_t k = row * n + t;
-    auto at = [&](int64_t addr) { return reinterpret_cast<float*>(addr) + p0; };
+    auto at = [&](int64_t addr) { return global_ptr<float>(addr) + p0; };
     const float* anchor = at(v.anchor[t]);
-    auto* params = reinterpret_cast<typename PS::T*>(v.params[k]) + p0;
+    auto* params = global_ptr<typename PS::T>(v.params[k]) + p0;
     float* mom2 = v.mom2[k] != 0 ? at(v.mom2[k]) : nullptr;
     float* slow = row == 0 && v.slow[t] != 0 ? at(v.slow[t]) : nullptr;
     for_lanes(p0, P, [&](auto lanes, int n) {

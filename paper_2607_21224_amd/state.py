@@ -200,6 +200,7 @@ class CpdpState:
                            _on(stream))
 
     METHODS = ("cpdp", "localsgd", "ddp")
+    LOCAL_RUN = 8  # local steps one launch takes at most
 
     # ---- general optimizers (SGD with weight decay, AdamW) -------------------
 
@@ -294,20 +295,45 @@ class CpdpState:
         """Capture steps t0 .. t0+len(grads)-1 (cadence decided now) as table
         steps into a HIP graph.  Every replay runs them with the table's next
         len(grads) entries, so a graph of one period replays successive
-        periods of a schedule.  Returns (graph, kinds)."""
+        periods of a schedule.  Returns (graph, kinds).
+
+        A replay leaves what step_table calls leave; between its first and
+        last step the state stays on the chip where it can: consecutive local
+        steps are one launch, and the table advances once, at the end."""
         for g in grads:
             self._check_grads(g, fp32_only=True)
+        if method not in self.METHODS:
+            raise ValueError(method)
+        h = table.handle
+        if h.update == 2 and self.mom2 is None:
+            raise ValueError("an AdamW step table needs the state initialised by init_opt(adamw)")
+        mom2 = self.mom2 if h.update == 2 else None
+        sync = [method == "ddp" or cpdp.cpdp_is_sync_step(t0 + j, self.K, T)
+                for j in range(len(grads))]
+        kinds = ["reconcile" if s else "local" for s in sync]
         graph = torch.cuda.CUDAGraph()
-        kinds = []
         side = torch.cuda.Stream()
         side.wait_stream(torch.cuda.current_stream())
         with torch.cuda.stream(side):
             torch.cuda.synchronize()
             with torch.cuda.graph(graph, stream=side):
                 cs = torch.cuda.current_stream()
-                for j, g in enumerate(grads):
-                    kinds.append(self.step_table(t0 + j, g, table, T, stream=cs, method=method,
-                                                 flags=flags))
+                j = 0
+                while j < len(grads) and j < table.n:  # later steps change nothing
+                    if sync[j]:
+                        cpdp.cpdp_sync_step_table_ahead(
+                            method, self.params, self.mom, mom2, grads[j], self.slow_mom,
+                            self.anchor, self.W, self.P, self.ld, self.K, h, j, flags,
+                            self.param_dt, cs)
+                        j += 1
+                        continue
+                    end = j + 1
+                    while end < len(grads) and not sync[end] and end - j < self.LOCAL_RUN:
+                        end += 1
+                    cpdp.cpdp_local_steps_table(self.params, self.mom, mom2, grads[j:end], self.W,
+                                                self.P, self.ld, self.K, h, j, self.param_dt, cs)
+                    j = end
+                cpdp.cpdp_step_table_advance_by(h, len(grads), cs)
         torch.cuda.current_stream().wait_stream(side)
         return graph, kinds
 
