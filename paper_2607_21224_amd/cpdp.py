@@ -201,6 +201,16 @@ def _torch_dtypes():
 
 _TORCH_DTYPE = _torch_dtypes()
 
+# torch type and bytes of a storage type, by name and by code
+_STORAGE = {k: (_TORCH_DTYPE[c], 2 if c == CPDP_BF16 else 4)
+            for name, c in DTYPES.items() for k in (name, c)}
+
+
+def _storage(dt):
+    """The same for any other way to write a storage type."""
+    code = DTYPES[dt] if isinstance(dt, str) else int(dt)
+    return _TORCH_DTYPE.get(code), 2 if code == CPDP_BF16 else 4
+
 
 def _span(x, n_elems: int, dt, name: str):
     """Address of a buffer argument the call touches for n_elems elements of
@@ -213,15 +223,12 @@ def _span(x, n_elems: int, dt, name: str):
     launch.)"""
     if x is None or isinstance(x, int):
         return x
-    code = DTYPES[dt] if isinstance(dt, str) else int(dt)
-    want = _TORCH_DTYPE.get(code)
+    want, size = _STORAGE.get(dt) or _storage(dt)
     if want is not None and x.dtype is not want:
         raise ValueError(f"{name}: storage type {want} expected, the tensor is {x.dtype}")
-    if n_elems > 0:
-        need = n_elems * (2 if code == CPDP_BF16 else 4)
-        have = x.numel() * x.element_size()
-        if have < need:
-            raise ValueError(f"{name}: the call touches {need} bytes, the tensor holds {have}")
+    if n_elems > 0 and x.nbytes < n_elems * size:
+        raise ValueError(f"{name}: the call touches {n_elems * size} bytes, "
+                         f"the tensor holds {x.nbytes}")
     if not x.is_cuda:
         raise ValueError(f"CPDP buffers must be device tensors, got one on {x.device}")
     if not x.is_contiguous():
@@ -229,11 +236,14 @@ def _span(x, n_elems: int, dt, name: str):
     return x.data_ptr()
 
 
+def _extent(W, P, ld) -> int:
+    """Elements from the first to the last one a W-row family (row stride ld,
+    P coordinates per row) uses."""
+    return (W - 1) * ld + P if W >= 1 and P > 0 and ld >= P else 0
+
+
 def _rows(x, W, P, ld, dt, name: str):
-    """A W-row family (row stride ld, P coordinates per row)."""
-    W, P, ld = int(W), int(P), int(ld)
-    n = (W - 1) * ld + P if W >= 1 and P > 0 and ld >= P else 0
-    return _span(x, n, dt, name)
+    return _span(x, _extent(int(W), int(P), int(ld)), dt, name)
 
 
 def _vec(x, P, name: str, dt=CPDP_F32):
@@ -283,10 +293,12 @@ def cpdp_state_init(theta0, params, mom, slow_mom, anchor, W, P, ld, K,
 def cpdp_local_step(params, mom, grads, W, P, ld, K, lr, mu,
                     param_dt=CPDP_F32, grad_dt=CPDP_F32, mom_dt=CPDP_F32,
                     stream=None, check=True):
-    s = lib.cpdp_local_step(_rows(params, W, P, ld, param_dt, "params"),
-                            _rows(mom, W, P, ld, mom_dt, "mom"),
-                            _rows(grads, W, P, ld, grad_dt, "grads"), int(W),
-                            int(P), int(ld), int(K), float(lr), float(mu),
+    W, P, ld = int(W), int(P), int(ld)
+    n = _extent(W, P, ld)
+    s = lib.cpdp_local_step(_span(params, n, param_dt, "params"),
+                            _span(mom, n, mom_dt, "mom"),
+                            _span(grads, n, grad_dt, "grads"), W,
+                            P, ld, int(K), float(lr), float(mu),
                             _dt(param_dt), _dt(grad_dt), _dt(mom_dt),
                             _stream(stream))
     return _done(s, "cpdp_local_step", check)
@@ -295,11 +307,13 @@ def cpdp_local_step(params, mom, grads, W, P, ld, K, lr, mu,
 def cpdp_reconcile(params, mom, grads, slow_mom, anchor, W, P, ld, K, lr, mu,
                    beta, alpha, param_dt=CPDP_F32, grad_dt=CPDP_F32,
                    mom_dt=CPDP_F32, stream=None, check=True):
-    s = lib.cpdp_reconcile(_rows(params, W, P, ld, param_dt, "params"),
-                           _rows(mom, W, P, ld, mom_dt, "mom"),
-                           _rows(grads, W, P, ld, grad_dt, "grads"),
-                           _vec(slow_mom, P, "slow_mom"), _vec(anchor, P, "anchor"), int(W), int(P),
-                           int(ld), int(K), float(lr), float(mu), float(beta),
+    W, P, ld = int(W), int(P), int(ld)
+    n = _extent(W, P, ld)
+    s = lib.cpdp_reconcile(_span(params, n, param_dt, "params"),
+                           _span(mom, n, mom_dt, "mom"),
+                           _span(grads, n, grad_dt, "grads"),
+                           _span(slow_mom, P, CPDP_F32, "slow_mom"),
+                           _span(anchor, P, CPDP_F32, "anchor"), W, P, ld, int(K), float(lr), float(mu), float(beta),
                            float(alpha), _dt(param_dt), _dt(grad_dt),
                            _dt(mom_dt), _stream(stream))
     return _done(s, "cpdp_reconcile", check)
@@ -308,10 +322,12 @@ def cpdp_reconcile(params, mom, grads, slow_mom, anchor, W, P, ld, K, lr, mu,
 def cpdp_localsgd_sync(params, mom, grads, anchor, W, P, ld, K, lr, mu,
                        param_dt=CPDP_F32, grad_dt=CPDP_F32, mom_dt=CPDP_F32,
                        stream=None, check=True):
-    s = lib.cpdp_localsgd_sync(_rows(params, W, P, ld, param_dt, "params"),
-                               _rows(mom, W, P, ld, mom_dt, "mom"),
-                               _rows(grads, W, P, ld, grad_dt, "grads"),
-                               _vec(anchor, P, "anchor"), int(W), int(P), int(ld), int(K),
+    W, P, ld = int(W), int(P), int(ld)
+    n = _extent(W, P, ld)
+    s = lib.cpdp_localsgd_sync(_span(params, n, param_dt, "params"),
+                               _span(mom, n, mom_dt, "mom"),
+                               _span(grads, n, grad_dt, "grads"),
+                               _span(anchor, P, CPDP_F32, "anchor"), W, P, ld, int(K),
                                float(lr), float(mu), _dt(param_dt), _dt(grad_dt),
                                _dt(mom_dt), _stream(stream))
     return _done(s, "cpdp_localsgd_sync", check)
@@ -319,10 +335,12 @@ def cpdp_localsgd_sync(params, mom, grads, anchor, W, P, ld, K, lr, mu,
 
 def cpdp_ddp_step(params, mom, grads, W, P, ld, lr, mu, param_dt=CPDP_F32,
                   grad_dt=CPDP_F32, mom_dt=CPDP_F32, stream=None, check=True):
-    s = lib.cpdp_ddp_step(_rows(params, W, P, ld, param_dt, "params"),
-                          _rows(mom, W, P, ld, mom_dt, "mom"),
-                          _rows(grads, W, P, ld, grad_dt, "grads"), int(W),
-                          int(P), int(ld), float(lr), float(mu), _dt(param_dt),
+    W, P, ld = int(W), int(P), int(ld)
+    n = _extent(W, P, ld)
+    s = lib.cpdp_ddp_step(_span(params, n, param_dt, "params"),
+                          _span(mom, n, mom_dt, "mom"),
+                          _span(grads, n, grad_dt, "grads"), W,
+                          P, ld, float(lr), float(mu), _dt(param_dt),
                           _dt(grad_dt), _dt(mom_dt), _stream(stream))
     return _done(s, "cpdp_ddp_step", check)
 
@@ -345,11 +363,13 @@ def cpdp_state_init_opt(theta0, params, mom, mom2, slow_mom, anchor, W, P, ld, K
 
 def cpdp_local_step_opt(params, mom, mom2, grads, W, P, ld, K, opt, param_dt=CPDP_F32,
                         stream=None, check=True):
-    s = lib.cpdp_local_step_opt(_rows(params, W, P, ld, param_dt, "params"),
-                                _rows(mom, W, P, ld, CPDP_F32, "mom"),
-                                _rows(mom2, W, P, ld, CPDP_F32, "mom2"),
-                                _rows(grads, W, P, ld, CPDP_F32, "grads"),
-                                int(W), int(P), int(ld), int(K), _opt(opt),
+    W, P, ld = int(W), int(P), int(ld)
+    n = _extent(W, P, ld)
+    s = lib.cpdp_local_step_opt(_span(params, n, param_dt, "params"),
+                                _span(mom, n, CPDP_F32, "mom"),
+                                _span(mom2, n, CPDP_F32, "mom2"),
+                                _span(grads, n, CPDP_F32, "grads"),
+                                W, P, ld, int(K), _opt(opt),
                                 _dt(param_dt), _stream(stream))
     return _done(s, "cpdp_local_step_opt", check)
 
@@ -358,12 +378,14 @@ def cpdp_sync_step_opt(strategy, params, mom, mom2, grads, slow_mom, anchor, W, 
                        opt, beta=0.0, alpha=1.0, flags=0, param_dt=CPDP_F32, stream=None,
                        check=True):
     strategy = SYNC_KINDS[strategy] if isinstance(strategy, str) else int(strategy)
-    s = lib.cpdp_sync_step_opt(strategy, _rows(params, W, P, ld, param_dt, "params"),
-                               _rows(mom, W, P, ld, CPDP_F32, "mom"),
-                               _rows(mom2, W, P, ld, CPDP_F32, "mom2"),
-                               _rows(grads, W, P, ld, CPDP_F32, "grads"),
-                               _vec(slow_mom, P, "slow_mom"), _vec(anchor, P, "anchor"), int(W),
-                               int(P), int(ld), int(K), _opt(opt), float(beta),
+    W, P, ld = int(W), int(P), int(ld)
+    n = _extent(W, P, ld)
+    s = lib.cpdp_sync_step_opt(strategy, _span(params, n, param_dt, "params"),
+                               _span(mom, n, CPDP_F32, "mom"),
+                               _span(mom2, n, CPDP_F32, "mom2"),
+                               _span(grads, n, CPDP_F32, "grads"),
+                               _span(slow_mom, P, CPDP_F32, "slow_mom"),
+                               _span(anchor, P, CPDP_F32, "anchor"), W, P, ld, int(K), _opt(opt), float(beta),
                                float(alpha), int(flags), _dt(param_dt), _stream(stream))
     return _done(s, "cpdp_sync_step_opt", check)
 

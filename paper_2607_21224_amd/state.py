@@ -346,11 +346,10 @@ class CpdpState:
             self._count = torch.zeros(1, dtype=torch.int64, device=self.params.device)
         cpdp.cpdp_count_unsynced(self.params, self.anchor, self.W, self.P, self.ld, self._count,
                                  self.param_dt, _on(stream))
+        # reading the word waits for the current stream by itself
         if isinstance(stream, torch.cuda.Stream):
             stream.synchronize()
-        elif stream is None:
-            torch.cuda.current_stream().synchronize()
-        else:
+        elif stream is not None:
             torch.cuda.synchronize(self.params.device)
         return int(self._count.item())
 
@@ -419,7 +418,7 @@ class CpdpState:
         want = torch.bfloat16 if self.grad_dt == "bf16" else torch.float32
         if g.dtype != want or not g.is_contiguous():
             raise ValueError(f"grads must be a contiguous {want} tensor")
-        if tuple(g.shape) != (self.W, self.ld):
+        if g.shape != (self.W, self.ld):
             raise ValueError(f"grads must have shape {(self.W, self.ld)}, got {tuple(g.shape)}")
         if g.device != self.params.device:
             raise ValueError(f"grads are on {g.device}, the state on {self.params.device}")
