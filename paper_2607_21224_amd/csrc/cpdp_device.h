@@ -347,6 +347,18 @@ __device__ __forceinline__ int64_t plan_tensor(const PlanView& v, int n, int64_t
     return lo;
 }
 
+// The same by a binary search with scalar loads: a longer chain, but one that
+// costs the vector memory path nothing.
+__device__ __forceinline__ int64_t plan_tensor_scalar(const PlanView& v, int n, int64_t b) {
+    int lo = 0, hi = n;
+    while (hi - lo > 1) {
+        const int mid = (lo + hi) >> 1;
+        if (v.chunk_start[mid] <= b) lo = mid;
+        else hi = mid;
+    }
+    return lo;
+}
+
 // ---- block order of the local step ---------------------------------------------
 //
 // The local step's blocks are the cells (replica row, column of kBlock * kVec

@@ -9,6 +9,8 @@
 namespace cpdp {
 namespace {
 
+constexpr unsigned kWaveSearchBlocks = 6144;
+
 // cell (row, chunk b), in the local step's block order -> replica row, tensor t,
 // its chunk
 template <Opt O, class PS, class Src>
@@ -21,7 +23,13 @@ __global__ __launch_bounds__(kBlock) void local_step_plan_kernel(Src src,
     const PlanView v = plan_view(plan, W, n);
     const int64_t row = cell / total_chunks;
     const int64_t b = cell - row * total_chunks;
-    const int64_t t = plan_tensor(v, n, b);
+    // Which search: while the launch is about one round of wavefronts, each
+    // block's chain of loads is the time; beyond, other blocks hide it and the
+    // 64-lane loads cost more than they save (local SGD step of 4 x 50,001
+    // coordinates in 200 tensors, 4 x 271,117 in 62 and 2 x 1,000,001 in 100:
+    // 3.4, 5.3 and 8.6 us by the wavefront, 3.9, 5.6 and 8.1 by the scalar search)
+    const int64_t t = gridDim.x <= kWaveSearchBlocks ? plan_tensor(v, n, b)
+                                                     : plan_tensor_scalar(v, n, b);
     // the tensor's size and its four addresses come in one round trip: behind
     // the test of p0 the addresses would take a second one
     const int64_t k = row * n + t;
