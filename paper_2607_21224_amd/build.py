@@ -29,8 +29,8 @@ KERNEL_SOURCES = ("kernels_flat.hip", "kernels_sync_cpdp.hip", "kernels_sync_loc
                   "kernels_sync_ddp.hip", "kernels_plan.hip", "kernels_plan_table.hip",
                   "kernels_table.hip", "kernels_check.hip")
 # headers the kernel sources include (part of what the recorded traffic is for)
-KERNEL_HEADERS = ("cpdp_device.h", "cpdp_sync_impl.h", "cpdp_split.h", "cpdp_plan_impl.h",
-                  "cpdp_launch.h")
+KERNEL_HEADERS = ("cpdp_device.h", "cpdp_sync_impl.h", "cpdp_split.h", "cpdp_dispatch.h",
+                  "cpdp_plan_impl.h", "cpdp_launch.h")
 HOST_SOURCES = ("cpdp_api.cpp",)
 # the library's own device memory (no kernels): the static plan table
 SCRATCH_SOURCES = ("plan_scratch.hip",)

@@ -28,14 +28,11 @@
 #pragma once
 
 #include "cpdp_device.h"
+#include "cpdp_dispatch.h"
 
 namespace cpdp {
 namespace {
 
-// Threads of a block at most: 16 groups of one wavefront.  With 8 groups (two
-// replicas a group at W = 16) the reconcile of 16 x 23.9 M fp32 coordinates
-// took 1433 us instead of 1361, with 4 groups (four replicas each) 1431.
-constexpr int kSplitThreads = 1024;
 constexpr int kSplitGroups = kSplitThreads / kBlock;
 constexpr int kCoords = kBlock * kVec;  // coordinates of a block
 
@@ -197,13 +194,6 @@ __device__ __forceinline__ void split_dispatch(const Src& src, const Rows& r, fl
         split_chunk<M, O, R, PS, kTiny, EXTRA>(src, r, slow, anchor, W, q0, P, inv_w, flags, lds);
 }
 
-// Replicas the split step takes: at W = 1 and 2 there is nothing to split (the
-// thread-per-coordinate kernel is up to 0.4 us faster on small states and
-// level on large ones); 32 are two rows a group of 16 and 32 KB of LDS.
-constexpr int kSplitMinW = 3;
-constexpr int kSplitMaxW = 2 * kSplitGroups;
-inline bool can_split(int W) { return W >= kSplitMinW && W <= kSplitMaxW; }
-
 // Replicas a group holds: one up to 16, then two, or four where the
 // parameters are bf16 and a row is half as long (W = 32, all rows bf16, 1.0 M
 // coordinates: 65 us with four, 72 with two; with fp32 rows 196 against 189 at
@@ -220,7 +210,7 @@ int launch_split(void (*kernel)(Args...), int64_t blocks, int W, int R, void* st
                  typename same_type<Args>::type... args) {
     void* argv[] = {static_cast<void*>(&args)...};
     return (int)hipLaunchKernel(reinterpret_cast<const void*>(kernel), dim3((unsigned)blocks),
-                                dim3((unsigned)((W + R - 1) / R * kBlock)), argv,
+                                dim3((unsigned)split_threads(W, R, kBlock)), argv,
                                 (size_t)W * kCoords * sizeof(float),
                                 static_cast<hipStream_t>(stream));
 }

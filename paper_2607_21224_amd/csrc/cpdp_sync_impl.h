@@ -43,7 +43,9 @@ int sync_w(const OptParams& o, const SyncArgs& a) {
 }
 
 // Which kernel takes the step.  The split one, except
-//  * W outside its range (W = 1 and 2, and more than 32 replicas);
+//  * W outside its range (W = 1 and 2, and more than 32 replicas), or so many
+//    coordinates that its blocks of up to 1024 threads pass the 2^32 work items
+//    of a launch (W * P >= 2^34 up to 16 replicas);
 //  * fp32 momentum SGD on 4, 8 or 16 replicas when the rows stay in the 256 MB
 //    last-level cache from one call to the next and the thread-per-coordinate
 //    kernel has a wavefront for every SIMD (1024 of them): the blocks of the
@@ -67,10 +69,11 @@ int sync_t(const OptParams& o, const SyncArgs& a) {
     constexpr bool plain = kPlainRows<M, O, PS, GS, MS>;
     const DirectScalars src{o, a.beta, a.alpha * o.lr};
     const bool cached = a.P < kCachedElems / a.W;
+    const bool splits = can_split(a.W, blocks_for(a.P), kBlock);
     if constexpr (std::is_same<GS, ParamF32>::value && std::is_same<MS, ParamF32>::value) {
         if (a.flags != 0) {
             const bool split = M != Sync::DDP || !(a.flags & kSyncWriteGbar) || cached;
-            return can_split(a.W) && split ? sync_split<M, O, PS, true, GS, MS>(src, a)
+            return splits && split ? sync_split<M, O, PS, true, GS, MS>(src, a)
                                            : sync_w<M, O, 0, PS, true>(o, a);
         }
     }
@@ -83,7 +86,7 @@ int sync_t(const OptParams& o, const SyncArgs& a) {
             if (a.W == 16) return sync_w<M, O, 16, PS, false, GS, MS>(o, a);
         }
     }
-    if (can_split(a.W)) return sync_split<M, O, PS, false, GS, MS>(src, a);
+    if (splits) return sync_split<M, O, PS, false, GS, MS>(src, a);
     return sync_w<M, O, 0, PS, false, GS, MS>(o, a);
 }
 

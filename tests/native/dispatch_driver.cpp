@@ -1,0 +1,54 @@
+// Checks the dispatch of the synchronisation steps (cpdp_dispatch.h) over
+// replica counts and sizes: whatever kernel a step goes to, its launch fits.
+// Exits non-zero on the first mismatch.
+#include <cstdio>
+#include <initializer_list>
+
+#include "cpdp_dispatch.h"
+
+static int failures = 0;
+#define CHECK(cond, W, P)                                                          \
+    do {                                                                           \
+        if (!(cond)) {                                                             \
+            std::printf("FAIL line %d: W %d P %lld: %s\n", __LINE__, (int)(W),     \
+                        (long long)(P), #cond);                                    \
+            ++failures;                                                            \
+        }                                                                          \
+    } while (0)
+
+int main() {
+    using namespace cpdp;
+    CHECK(launch_fits(0xFFFFFFFF / 64, 64), 0, 0);
+    CHECK(!launch_fits(((int64_t)1 << 32) / 64, 64), 0, 0);
+
+    for (int group : {64, 256}) {
+        const int64_t per_block = (int64_t)group * 4;
+        auto blocks = [&](int64_t P) { return (P + per_block - 1) / per_block; };
+        for (int W = 1; W <= 40; ++W)
+            for (int e = 0; e <= 34; ++e)
+                for (int64_t d : {-1, 0, 1}) {
+                    const int64_t P = ((int64_t)1 << e) + d;
+                    if (P < 1) continue;
+                    const bool split = can_split(W, blocks(P), group);
+                    for (int R : {1, 2, 4}) {
+                        const int64_t threads = split_threads(W, R, group);
+                        if (split && threads <= kSplitThreads)
+                            CHECK(launch_fits(blocks(P), threads), W, P);
+                    }
+                    // sizes that fit stay with the split step
+                    if (W >= kSplitMinW && W <= split_max_w(group) && P <= ((int64_t)1 << 29))
+                        CHECK(split, W, P);
+                    if (W < kSplitMinW || W > split_max_w(group)) CHECK(!split, W, P);
+                }
+    }
+    // states of about 120 to 215 GB on one GPU: 16 replicas of 2^30 coordinates
+    // and 8 of 2^31 have one thread too many for the split step, and fit the
+    // one-wavefront blocks of the thread-per-coordinate kernel
+    CHECK(!can_split(16, ((int64_t)1 << 30) / 256, 64), 16, (int64_t)1 << 30);
+    CHECK(!can_split(8, ((int64_t)1 << 31) / 256, 64), 8, (int64_t)1 << 31);
+    CHECK(can_split(16, ((int64_t)1 << 30) / 256 - 1, 64), 16, (int64_t)1 << 30);
+    CHECK(launch_fits(((int64_t)1 << 30) / 256, 64), 16, (int64_t)1 << 30);
+    CHECK(launch_fits(((int64_t)1 << 31) / 256, 64), 8, (int64_t)1 << 31);
+    std::printf("%s\n", failures ? "FAILED" : "OK");
+    return failures ? 1 : 0;
+}

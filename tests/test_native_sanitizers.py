@@ -40,3 +40,12 @@ def test_oracle_under_sanitizers(tmp_path):
           os.path.join(NATIVE, "oracle_driver.c"), "-lm", "-o", exe])
     out = _run([exe], env=dict(os.environ, ASAN_OPTIONS="detect_leaks=1"))
     assert "oracle checksum" in out
+
+
+def test_dispatch_of_synchronisation_steps(tmp_path):
+    """Every launch of a synchronisation step holds fewer than 2^32 work items,
+    and no size that a kernel could take is refused for it."""
+    exe = str(tmp_path / "dispatch_driver")
+    _run(["g++", "-std=c++17", *SAN, "-I", os.path.join(ROOT, "paper_2607_21224_amd", "csrc"),
+          os.path.join(NATIVE, "dispatch_driver.cpp"), "-o", exe])
+    assert _run([exe]).strip() == "OK"
