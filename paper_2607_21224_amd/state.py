@@ -346,11 +346,15 @@ class CpdpState:
             self._count = torch.zeros(1, dtype=torch.int64, device=self.params.device)
         cpdp.cpdp_count_unsynced(self.params, self.anchor, self.W, self.P, self.ld, self._count,
                                  self.param_dt, _on(stream))
-        # reading the word waits for the current stream by itself
+        # Reading the word waits for the current stream of the device the word
+        # is on.  The count ran on the stream given, or on the current stream of
+        # the current device, which need not be the state's.
         if isinstance(stream, torch.cuda.Stream):
             stream.synchronize()
         elif stream is not None:
             torch.cuda.synchronize(self.params.device)
+        elif torch.cuda.current_device() != self.params.device.index:
+            torch.cuda.current_stream().synchronize()
         return int(self._count.item())
 
     # ---- HIP graph capture of a period --------------------------------------------
