@@ -703,9 +703,7 @@ int cpdp_step_table_set_position(const cpdp_step_table* t, int64_t position, voi
 }
 
 int cpdp_step_table_advance(const cpdp_step_table* t, void* stream) {
-    cpdp::Opt kind;
-    if (int s = check_step_table(t, &kind)) return s;
-    return hip_status(cpdp::launch_step_table_advance(static_cast<int64_t*>(t->table), stream));
+    return cpdp_step_table_advance_by(t, 1, stream);
 }
 
 int cpdp_step_table_position(const cpdp_step_table* t, int64_t* position) {
@@ -714,24 +712,6 @@ int cpdp_step_table_position(const cpdp_step_table* t, int64_t* position) {
     if (position == nullptr) return CPDP_ERR_NULL;
     return hip_status(
         cpdp::read_step_table_position(static_cast<const int64_t*>(t->table), position));
-}
-
-int cpdp_local_step_table(void* params, void* mom, void* mom2, const void* grads, int W,
-                          int64_t P, int64_t ld, int K, const cpdp_step_table* t, int param_dt,
-                          void* stream) {
-    if (int s = check_shape(W, P, ld, K)) return s;
-    cpdp::Opt kind;
-    if (int s = check_step_table(t, &kind)) return s;
-    if (!is_dtype(param_dt)) return CPDP_ERR_DTYPE;
-    if (P == 0) return CPDP_OK;
-    if (!cpdp::grid_fits(W, P)) return CPDP_ERR_INVALID_ARG;
-    const bool adam = kind == cpdp::Opt::ADAMW;
-    if (int s = check_local_ptrs(params, mom, mom2, grads, W, P, ld, esize(param_dt), adam))
-        return s;
-    return hip_status(cpdp::launch_local_step_table(
-        kind, param_kind(param_dt), static_cast<const int64_t*>(t->table), params,
-        static_cast<float*>(mom), adam ? static_cast<float*>(mom2) : nullptr,
-        static_cast<const float*>(grads), W, P, ld, stream));
 }
 
 int cpdp_local_steps_table(void* params, void* mom, void* mom2, const void* const* grads,
@@ -759,32 +739,16 @@ int cpdp_local_steps_table(void* params, void* mom, void* mom2, const void* cons
         ld, stream));
 }
 
-int cpdp_sync_step_table(int strategy, void* params, void* mom, void* mom2, void* grads,
-                         float* slow_mom, float* anchor, int W, int64_t P, int64_t ld, int K,
-                         const cpdp_step_table* t, unsigned flags, int param_dt, void* stream) {
-    if (int s = check_shape(W, P, ld, K)) return s;
-    if (flags & ~kKnownFlags) return CPDP_ERR_INVALID_ARG;
-    if (!valid_strategy(strategy)) return CPDP_ERR_INVALID_ARG;
-    cpdp::Opt kind;
-    if (int s = check_step_table(t, &kind)) return s;
-    if (!is_dtype(param_dt)) return CPDP_ERR_DTYPE;
-    if (P == 0) return CPDP_OK;
-    if (!cpdp::grid_fits(1, P)) return CPDP_ERR_INVALID_ARG;
-    float* slow;
-    float* anc;
-    void* m2;
-    if (int s = check_sync_ptrs(strategy, kind == cpdp::Opt::ADAMW, params, mom, mom2, grads,
-                                slow_mom, anchor, W, P, ld, esize(param_dt), &slow, &anc, &m2))
-        return s;
-    return hip_status(cpdp::launch_sync_table(
-        sync_mode(strategy), kind, param_kind(param_dt), static_cast<const int64_t*>(t->table),
-        params, static_cast<float*>(mom), static_cast<float*>(m2),
-        static_cast<const float*>(grads), slow, anc, W, P, ld, flags, stream));
+int cpdp_local_step_table(void* params, void* mom, void* mom2, const void* grads, int W,
+                          int64_t P, int64_t ld, int K, const cpdp_step_table* t, int param_dt,
+                          void* stream) {
+    return cpdp_local_steps_table(params, mom, mom2, &grads, 1, W, P, ld, K, t, 0, param_dt,
+                                  stream);
 }
 
 int cpdp_sync_step_table_ahead(int strategy, void* params, void* mom, void* mom2, void* grads,
-                         float* slow_mom, float* anchor, int W, int64_t P, int64_t ld, int K,
-                         const cpdp_step_table* t, int64_t ahead, unsigned flags,
+                               float* slow_mom, float* anchor, int W, int64_t P, int64_t ld,
+                               int K, const cpdp_step_table* t, int64_t ahead, unsigned flags,
                                int param_dt, void* stream) {
     if (int s = check_shape(W, P, ld, K)) return s;
     if (flags & ~kKnownFlags) return CPDP_ERR_INVALID_ARG;
@@ -805,6 +769,13 @@ int cpdp_sync_step_table_ahead(int strategy, void* params, void* mom, void* mom2
         sync_mode(strategy), kind, param_kind(param_dt), static_cast<const int64_t*>(t->table),
         ahead, params, static_cast<float*>(mom), static_cast<float*>(m2),
         static_cast<const float*>(grads), slow, anc, W, P, ld, flags, stream));
+}
+
+int cpdp_sync_step_table(int strategy, void* params, void* mom, void* mom2, void* grads,
+                         float* slow_mom, float* anchor, int W, int64_t P, int64_t ld, int K,
+                         const cpdp_step_table* t, unsigned flags, int param_dt, void* stream) {
+    return cpdp_sync_step_table_ahead(strategy, params, mom, mom2, grads, slow_mom, anchor, W, P,
+                                      ld, K, t, 0, flags, param_dt, stream);
 }
 
 int cpdp_step_table_advance_by(const cpdp_step_table* t, int64_t steps, void* stream) {

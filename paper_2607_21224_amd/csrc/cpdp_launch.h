@@ -109,31 +109,17 @@ inline int64_t step_table_bytes(int n_steps) {
            (int64_t)n_steps * (int64_t)sizeof(StepEntry);
 }
 
-int launch_local_step_table(Opt opt, Param pt, const int64_t* table, void* params, float* mom,
-                            float* mom2, const float* grads, int W, int64_t P, int64_t ld,
-                            void* stream);
-
-int launch_sync_table(Sync mode, Opt opt, Param pt, const int64_t* table, void* params,
-                      float* mom, float* mom2, const float* grads, float* slow, float* anchor,
-                      int W, int64_t P, int64_t ld, unsigned flags, void* stream);
-
-// What a captured run of table steps uses: J consecutive local steps in one
-// launch, a synchronisation step, both with the entries `ahead` places past the
-// position, and an advance over all of them.  Weak, so that a host-only build
-// of the validation layer may do without them.
+// Steps with the scalars of a step table: J (1 to kMaxLocalSteps) consecutive
+// local steps in one launch, step j with the gradient rows grads[j]; a
+// synchronisation step; both with the entries `ahead` places past the position.
 constexpr int kMaxLocalSteps = 8;
-__attribute__((weak)) int launch_local_steps_table(Opt opt, Param pt, const int64_t* table,
-                                                   int64_t ahead, void* params, float* mom,
-                                                   float* mom2, const float* const* grads, int J,
-                                                   int W, int64_t P, int64_t ld, void* stream);
-__attribute__((weak)) int launch_sync_table_ahead(Sync mode, Opt opt, Param pt,
-                                                  const int64_t* table, int64_t ahead,
-                                                  void* params, float* mom, float* mom2,
-                                                  const float* grads, float* slow, float* anchor,
-                                                  int W, int64_t P, int64_t ld, unsigned flags,
-                                                  void* stream);
-__attribute__((weak)) int launch_step_table_advance_by(int64_t* table, int64_t steps,
-                                                       void* stream);
+int launch_local_steps_table(Opt opt, Param pt, const int64_t* table, int64_t ahead, void* params,
+                             float* mom, float* mom2, const float* const* grads, int J, int W,
+                             int64_t P, int64_t ld, void* stream);
+int launch_sync_table_ahead(Sync mode, Opt opt, Param pt, const int64_t* table, int64_t ahead,
+                            void* params, float* mom, float* mom2, const float* grads,
+                            float* slow, float* anchor, int W, int64_t P, int64_t ld,
+                            unsigned flags, void* stream);
 
 // Plan steps with the scalars of a step table's current entry.
 int launch_local_step_plan_table(Opt opt, Param pt, const int64_t* plan, int W, int n,
@@ -145,7 +131,7 @@ int launch_sync_plan_table(Sync mode, Opt opt, Param pt, const int64_t* plan, in
 // One-thread kernels on the table's position word (graph-capturable: no
 // memset, no copy).
 int launch_step_table_set(int64_t* table, int64_t position, void* stream);
-int launch_step_table_advance(int64_t* table, void* stream);
+int launch_step_table_advance_by(int64_t* table, int64_t steps, void* stream);
 
 // Synchronous device-to-host read of a table's position word.
 int read_step_table_position(const int64_t* table, int64_t* position);

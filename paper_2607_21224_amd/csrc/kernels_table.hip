@@ -160,13 +160,6 @@ int launch_local_steps_table(Opt opt, Param pt, const int64_t* table, int64_t ah
     }
 }
 
-int launch_local_step_table(Opt opt, Param pt, const int64_t* table, void* params, float* mom,
-                            float* mom2, const float* grads, int W, int64_t P, int64_t ld,
-                            void* stream) {
-    return launch_local_steps_table(opt, pt, table, 0, params, mom, mom2, &grads, 1, W, P, ld,
-                                    stream);
-}
-
 int launch_sync_table_ahead(Sync mode, Opt opt, Param pt, const int64_t* table, int64_t ahead,
                             void* params, float* mom, float* mom2, const float* grads, float* slow,
                             float* anchor, int W, int64_t P, int64_t ld, unsigned flags,
@@ -180,13 +173,6 @@ int launch_sync_table_ahead(Sync mode, Opt opt, Param pt, const int64_t* table, 
     }
 }
 
-int launch_sync_table(Sync mode, Opt opt, Param pt, const int64_t* table, void* params,
-                      float* mom, float* mom2, const float* grads, float* slow, float* anchor,
-                      int W, int64_t P, int64_t ld, unsigned flags, void* stream) {
-    return launch_sync_table_ahead(mode, opt, pt, table, 0, params, mom, mom2, grads, slow, anchor,
-                                   W, P, ld, flags, stream);
-}
-
 int launch_step_table_set(int64_t* table, int64_t position, void* stream) {
     void* argv[] = {static_cast<void*>(&table), static_cast<void*>(&position)};
     return (int)hipLaunchKernel(reinterpret_cast<const void*>(step_table_set_kernel), dim3(1),
@@ -197,10 +183,6 @@ int launch_step_table_advance_by(int64_t* table, int64_t steps, void* stream) {
     void* argv[] = {static_cast<void*>(&table), static_cast<void*>(&steps)};
     return (int)hipLaunchKernel(reinterpret_cast<const void*>(step_table_advance_kernel), dim3(1),
                                 dim3(64), argv, 0, static_cast<hipStream_t>(stream));
-}
-
-int launch_step_table_advance(int64_t* table, void* stream) {
-    return launch_step_table_advance_by(table, 1, stream);
 }
 
 int read_step_table_position(const int64_t* table, int64_t* position) {

@@ -175,12 +175,44 @@ int main() {
         EXPECT(cpdp_step_table_set_position(&tab, n, nullptr), CPDP_OK, true);
         EXPECT(cpdp_step_table_set_position(&tab, n + 1, nullptr), CPDP_ERR_INVALID_ARG, false);
         EXPECT(cpdp_step_table_set_position(&tab, -1, nullptr), CPDP_ERR_INVALID_ARG, false);
+        // runs of table steps: 1 to 8 gradient rows, each checked as a step's own
+        const void* rows[9];
+        for (auto& r : rows) r = gr;
+        EXPECT(cpdp_local_steps_table(pa, mo, m2, rows, 1, W, P, ld, 4, &tab, 0, 0, nullptr), CPDP_OK, true);
+        EXPECT(cpdp_local_steps_table(pa, mo, m2, rows, 8, W, P, ld, 4, &tab, n, 1, nullptr), CPDP_OK, true);
+        EXPECT(cpdp_local_steps_table(pa, mo, m2, rows, 0, W, P, ld, 4, &tab, 0, 0, nullptr), CPDP_ERR_INVALID_ARG, false);
+        EXPECT(cpdp_local_steps_table(pa, mo, m2, rows, 9, W, P, ld, 4, &tab, 0, 0, nullptr), CPDP_ERR_INVALID_ARG, false);
+        EXPECT(cpdp_local_steps_table(pa, mo, m2, rows, 2, W, P, ld, 4, &tab, -1, 0, nullptr), CPDP_ERR_INVALID_ARG, false);
+        EXPECT(cpdp_local_steps_table(pa, mo, m2, nullptr, 2, W, P, ld, 4, &tab, 0, 0, nullptr), CPDP_ERR_NULL, false);
+        EXPECT(cpdp_local_steps_table(pa, mo, nullptr, rows, 2, W, P, ld, 4, &tab, 0, 0, nullptr), CPDP_ERR_NULL, false);
+        EXPECT(cpdp_local_steps_table(pa, mo, m2, rows, 2, W, P, ld, 4, nullptr, 0, 0, nullptr), CPDP_ERR_NULL, false);
+        EXPECT(cpdp_local_steps_table(pa, mo, m2, rows, 2, W, P, ld, 0, &tab, 0, 0, nullptr), CPDP_ERR_INVALID_ARG, false);
+        EXPECT(cpdp_local_steps_table(pa, mo, m2, rows, 2, W, P, ld, 4, &tab, 0, 2, nullptr), CPDP_ERR_DTYPE, false);
+        EXPECT(cpdp_local_steps_table(pa, mo, m2, rows, 2, W, 0, ld, 4, &tab, 0, 0, nullptr), CPDP_OK, false);
+        rows[1] = mo;
+        EXPECT(cpdp_local_steps_table(pa, mo, m2, rows, 2, W, P, ld, 4, &tab, 0, 0, nullptr), CPDP_ERR_OVERLAP, false);
+        rows[1] = nullptr;
+        EXPECT(cpdp_local_steps_table(pa, mo, m2, rows, 2, W, P, ld, 4, &tab, 0, 0, nullptr), CPDP_ERR_NULL, false);
+        rows[1] = static_cast<const char*>(gr) + 4;
+        EXPECT(cpdp_local_steps_table(pa, mo, m2, rows, 2, W, P, ld, 4, &tab, 0, 0, nullptr), CPDP_ERR_MISALIGNED, false);
+        EXPECT(cpdp_local_steps_table(pa, mo, m2, rows, 1, W, P, ld, 4, &tab, 0, 0, nullptr), CPDP_OK, true);
+        EXPECT(cpdp_sync_step_table_ahead(0, pa, mo, m2, gr, u, an, W, P, ld, 4, &tab, n, 3u, 0, nullptr), CPDP_OK, true);
+        EXPECT(cpdp_sync_step_table_ahead(0, pa, mo, m2, gr, u, an, W, P, ld, 4, &tab, -1, 0u, 0, nullptr), CPDP_ERR_INVALID_ARG, false);
+        EXPECT(cpdp_sync_step_table_ahead(0, pa, mo, m2, gr, nullptr, an, W, P, ld, 4, &tab, 1, 0u, 0, nullptr), CPDP_ERR_NULL, false);
+        EXPECT(cpdp_sync_step_table_ahead(0, pa, mo, m2, gr, u, an, W, P, ld, 4, &tab, 1, 16u, 0, nullptr), CPDP_ERR_INVALID_ARG, false);
+        EXPECT(cpdp_step_table_advance_by(&tab, 0, nullptr), CPDP_OK, true);
+        EXPECT(cpdp_step_table_advance_by(&tab, 1000, nullptr), CPDP_OK, true);
+        EXPECT(cpdp_step_table_advance_by(&tab, -1, nullptr), CPDP_ERR_INVALID_ARG, false);
+        EXPECT(cpdp_step_table_advance_by(nullptr, 1, nullptr), CPDP_ERR_NULL, false);
         int64_t pos = -1;
         EXPECT(cpdp_step_table_position(&tab, &pos), CPDP_OK, false);
         EXPECT(cpdp_step_table_position(&tab, nullptr), CPDP_ERR_NULL, false);
         tab.n_steps += 1;  // an edited handle is rejected everywhere
         EXPECT(cpdp_local_step_table(pa, mo, m2, gr, W, P, ld, 4, &tab, 0, nullptr), CPDP_ERR_INVALID_ARG, false);
         EXPECT(cpdp_step_table_advance(&tab, nullptr), CPDP_ERR_INVALID_ARG, false);
+        EXPECT(cpdp_step_table_advance_by(&tab, 2, nullptr), CPDP_ERR_INVALID_ARG, false);
+        EXPECT(cpdp_local_steps_table(pa, mo, m2, rows, 1, W, P, ld, 4, &tab, 0, 0, nullptr), CPDP_ERR_INVALID_ARG, false);
+        EXPECT(cpdp_sync_step_table_ahead(0, pa, mo, m2, gr, u, an, W, P, ld, 4, &tab, 0, 0u, 0, nullptr), CPDP_ERR_INVALID_ARG, false);
         tab.n_steps -= 1;
         tab.update = 0;
         EXPECT(cpdp_sync_step_table(0, pa, mo, m2, gr, u, an, W, P, ld, 4, &tab, 0u, 0, nullptr), CPDP_ERR_INVALID_ARG, false);

@@ -30,12 +30,13 @@ int launch_sync_plan(Sync, Opt, const OptParams&, Param, const int64_t*, int, in
                      float, unsigned, void*) {
     return ++g_launches, 0;
 }
-int launch_local_step_table(Opt, Param, const int64_t*, void*, float*, float*, const float*, int,
-                            int64_t, int64_t, void*) {
+int launch_local_steps_table(Opt, Param, const int64_t*, int64_t, void*, float*, float*,
+                             const float* const*, int, int, int64_t, int64_t, void*) {
     return ++g_launches, 0;
 }
-int launch_sync_table(Sync, Opt, Param, const int64_t*, void*, float*, float*, const float*,
-                      float*, float*, int, int64_t, int64_t, unsigned, void*) {
+int launch_sync_table_ahead(Sync, Opt, Param, const int64_t*, int64_t, void*, float*, float*,
+                            const float*, float*, float*, int, int64_t, int64_t, unsigned,
+                            void*) {
     return ++g_launches, 0;
 }
 int launch_local_step_plan_table(Opt, Param, const int64_t*, int, int, int64_t, const int64_t*,
@@ -47,7 +48,7 @@ int launch_sync_plan_table(Sync, Opt, Param, const int64_t*, int, int, int64_t, 
     return ++g_launches, 0;
 }
 int launch_step_table_set(int64_t*, int64_t, void*) { return ++g_launches, 0; }
-int launch_step_table_advance(int64_t*, void*) { return ++g_launches, 0; }
+int launch_step_table_advance_by(int64_t*, int64_t, void*) { return ++g_launches, 0; }
 int read_step_table_position(const int64_t*, int64_t* position) { return *position = 0, 0; }
 int64_t g_uploaded_bytes = 0;
 int upload_bytes(void*, const void*, int64_t bytes) { return g_uploaded_bytes = bytes, 0; }
