@@ -408,7 +408,9 @@ int cpdp_sync_step_table(int strategy, void* params, void* mom, void* mom2,
  *   cpdp_sync_step_table_ahead   cpdp_sync_step_table with the entry `ahead`
  *       places past the position.
  *   cpdp_step_table_advance_by   `steps` advances in one kernel.
- * ahead outside [0, n_steps of the table], steps < 0 or n_steps outside its
+ * How far the table reaches is read when a step runs, so a captured run may go
+ * past the entries the table has while it is captured.  ahead outside
+ * [0, 2^24], the most entries of a table, steps < 0 or n_steps outside its
  * range: CPDP_ERR_INVALID_ARG. */
 int cpdp_local_steps_table(void* params, void* mom, void* mom2,
                            const void* const* grads, int n_steps, int W, int64_t P,

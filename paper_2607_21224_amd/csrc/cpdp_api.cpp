@@ -221,6 +221,8 @@ uint64_t step_table_seal(const cpdp_step_table* t) {
     return h;
 }
 
+constexpr int kMaxTableSteps = 1 << 24;  // entries of a step table at most
+
 // A usable step-table handle: filled by cpdp_step_table_fill and unchanged.
 int check_step_table(const cpdp_step_table* t, cpdp::Opt* kind) {
     if (t == nullptr || t->table == nullptr) return CPDP_ERR_NULL;
@@ -664,7 +666,7 @@ int cpdp_step_table_fill(cpdp_step_table* t, int64_t table_bytes, int n_steps,
                          const cpdp_optimizer* opt, const float* beta, const float* alpha) {
     if (t == nullptr || t->table == nullptr || opt == nullptr) return CPDP_ERR_NULL;
     if ((reinterpret_cast<uintptr_t>(t->table) & 15u) != 0) return CPDP_ERR_MISALIGNED;
-    if (n_steps < 1 || n_steps > (1 << 24)) return CPDP_ERR_INVALID_ARG;
+    if (n_steps < 1 || n_steps > kMaxTableSteps) return CPDP_ERR_INVALID_ARG;
     const int64_t bytes = cpdp::step_table_bytes(n_steps);
     if (table_bytes < bytes) return CPDP_ERR_INVALID_ARG;
     std::vector<unsigned char> host((size_t)bytes, 0);
@@ -718,11 +720,11 @@ int cpdp_local_steps_table(void* params, void* mom, void* mom2, const void* cons
                            int n_steps, int W, int64_t P, int64_t ld, int K,
                            const cpdp_step_table* t, int64_t ahead, int param_dt, void* stream) {
     if (int s = check_shape(W, P, ld, K)) return s;
-    if (n_steps < 1 || n_steps > cpdp::kMaxLocalSteps || ahead < 0) return CPDP_ERR_INVALID_ARG;
+    if (n_steps < 1 || n_steps > cpdp::kMaxLocalSteps) return CPDP_ERR_INVALID_ARG;
+    if (ahead < 0 || ahead > kMaxTableSteps) return CPDP_ERR_INVALID_ARG;
     if (grads == nullptr) return CPDP_ERR_NULL;
     cpdp::Opt kind;
     if (int s = check_step_table(t, &kind)) return s;
-    if (ahead > t->n_steps) return CPDP_ERR_INVALID_ARG;
     if (!is_dtype(param_dt)) return CPDP_ERR_DTYPE;
     if (P == 0) return CPDP_OK;
     if (!cpdp::grid_fits(W, P)) return CPDP_ERR_INVALID_ARG;
@@ -755,7 +757,7 @@ int cpdp_sync_step_table_ahead(int strategy, void* params, void* mom, void* mom2
     if (!valid_strategy(strategy)) return CPDP_ERR_INVALID_ARG;
     cpdp::Opt kind;
     if (int s = check_step_table(t, &kind)) return s;
-    if (ahead < 0 || ahead > t->n_steps) return CPDP_ERR_INVALID_ARG;
+    if (ahead < 0 || ahead > kMaxTableSteps) return CPDP_ERR_INVALID_ARG;
     if (!is_dtype(param_dt)) return CPDP_ERR_DTYPE;
     if (P == 0) return CPDP_OK;
     if (!cpdp::grid_fits(1, P)) return CPDP_ERR_INVALID_ARG;

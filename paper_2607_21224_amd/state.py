@@ -319,7 +319,7 @@ class CpdpState:
             with torch.cuda.graph(graph, stream=side):
                 cs = torch.cuda.current_stream()
                 j = 0
-                while j < len(grads) and j < table.n:  # later steps change nothing
+                while j < len(grads):
                     if sync[j]:
                         cpdp.cpdp_sync_step_table_ahead(
                             method, self.params, self.mom, mom2, grads[j], self.slow_mom,

@@ -180,6 +180,11 @@ int main() {
         for (auto& r : rows) r = gr;
         EXPECT(cpdp_local_steps_table(pa, mo, m2, rows, 1, W, P, ld, 4, &tab, 0, 0, nullptr), CPDP_OK, true);
         EXPECT(cpdp_local_steps_table(pa, mo, m2, rows, 8, W, P, ld, 4, &tab, n, 1, nullptr), CPDP_OK, true);
+        // past the entries the handle has now: a refilled table may have more
+        EXPECT(cpdp_local_steps_table(pa, mo, m2, rows, 8, W, P, ld, 4, &tab, n + 1, 0, nullptr), CPDP_OK, true);
+        EXPECT(cpdp_local_steps_table(pa, mo, m2, rows, 8, W, P, ld, 4, &tab, (1 << 24) + 1, 0, nullptr), CPDP_ERR_INVALID_ARG, false);
+        EXPECT(cpdp_sync_step_table_ahead(0, pa, mo, m2, gr, u, an, W, P, ld, 4, &tab, n + 1, 0u, 0, nullptr), CPDP_OK, true);
+        EXPECT(cpdp_sync_step_table_ahead(0, pa, mo, m2, gr, u, an, W, P, ld, 4, &tab, (1 << 24) + 1, 0u, 0, nullptr), CPDP_ERR_INVALID_ARG, false);
         EXPECT(cpdp_local_steps_table(pa, mo, m2, rows, 0, W, P, ld, 4, &tab, 0, 0, nullptr), CPDP_ERR_INVALID_ARG, false);
         EXPECT(cpdp_local_steps_table(pa, mo, m2, rows, 9, W, P, ld, 4, &tab, 0, 0, nullptr), CPDP_ERR_INVALID_ARG, false);
         EXPECT(cpdp_local_steps_table(pa, mo, m2, rows, 2, W, P, ld, 4, &tab, -1, 0, nullptr), CPDP_ERR_INVALID_ARG, false);

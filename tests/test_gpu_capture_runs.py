@@ -4,6 +4,7 @@ a run, against the same steps called one by one, bit for bit."""
 import pytest
 import torch
 
+from paper_2607_21224_amd import cpdp
 from paper_2607_21224_amd.state import CpdpState, Optimizer, StepTable
 
 pytestmark = pytest.mark.gpu
@@ -51,3 +52,34 @@ def test_captured_runs_equal_single_steps(kind, param, method, W, P, K, table_st
         assert table.position() == min((period + 1) * K, table_steps)
         for x, y in zip(_bits(a), _bits(b)):
             assert torch.equal(x, y), (kind, param, method, period)
+
+
+def test_capture_before_the_table_is_refilled():
+    """A run captured while the table is shorter than the run, which then gets
+    all its entries: what a replay steps is decided when it runs."""
+    W, P, K = 4, 515, 4
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    theta = torch.randn(P, generator=gen, device="cuda") * 0.02
+    a, b = (CpdpState(W, P, K=K) for _ in range(2))
+    for st in (a, b):
+        st.init_opt(theta, _opt("sgd", 0))
+    grads = [torch.zeros((W, a.ld), device="cuda") for _ in range(K)]
+    for g in grads:
+        g[:, :P] = torch.randn((W, P), generator=gen, device="cuda") * 1e-3
+    table = StepTable([(_opt("sgd", s), s + 1, 0.5, 0.75) for s in range(K)])
+
+    def fill(n):
+        cpdp.cpdp_step_table_fill(table.handle, table.buf.numel(),
+                                  [_opt("sgd", s).c_struct(s + 1) for s in range(n)],
+                                  [0.5] * n, [0.75] * n)
+
+    fill(1)
+    graph, _ = b.capture_steps(grads, table)
+    fill(K)
+    graph.replay()
+    for j in range(K):
+        a.step_opt(j + 1, grads[j], _opt("sgd", j), 0.5, 0.75)
+    torch.cuda.synchronize()
+    assert table.position() == K
+    for x, y in zip(_bits(a), _bits(b)):
+        assert torch.equal(x, y)
