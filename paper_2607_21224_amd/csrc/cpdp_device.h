@@ -85,13 +85,20 @@ __device__ __forceinline__ void vstore(V* p, V v) {
 //   kRagged  P >= 4, the row's last wavefront: every lane loads 4 existing
 //            coordinates with one access, the ones past the end taking the
 //            row's last 4 (aligned to the element only) and shifting theirs
-//            into place; what they load of other lanes' coordinates, which
-//            those may already have updated, is dropped.  Loading the short lane's coordinates one by one
-//            behind a branch made a wave wait for each before it issued the
-//            next, W round trips to memory in a row (reconcile of 8 x 100,003
-//            bf16 coordinates: 15.0 us, so 8.9, both with the
-//            thread-per-coordinate kernel).
+//            into place.  The last 4 may belong to another lane, wavefront or
+//            block that has already updated them; what was loaded of them is
+//            dropped.  Loading the short lane's coordinates one by one behind
+//            a branch made a wave wait for each before it issued the next, W
+//            round trips to memory in a row (reconcile of 8 x 100,003 bf16
+//            coordinates: 15.0 us, so 8.9, both with the thread-per-coordinate
+//            kernel).
 //   kTiny    P < 4: one by one, the missing ones taking the last coordinate.
+//            Every kernel carries this code, so it must not cost the others
+//            registers: with the loads of a batch of replicas in flight, each
+//            with an address of its own, the run-time-W kernel needed 138
+//            registers for momentum SGD and 202 for AdamW (3 and 2 wavefronts a
+//            SIMD) instead of 78 and 117 (6 and 4).  So the loads are issued in
+//            order, and sync_chunk takes one replica at a time.
 // Nothing computed from a missing coordinate is stored.
 enum Lanes { kTiny, kFull, kRagged };
 
@@ -119,7 +126,10 @@ __device__ __forceinline__ void load_f32(const float* p, int n, float (&x)[kVec]
         shift_down(kVec - n, x);
     } else {
 #pragma unroll
-        for (int k = 0; k < kVec; ++k) x[k] = p[tail_index(k, n)];
+        for (int k = 0; k < kVec; ++k) {
+            x[k] = p[tail_index(k, n)];
+            __builtin_amdgcn_sched_barrier(0);
+        }
     }
 }
 
@@ -189,7 +199,10 @@ struct ParamBF16 {
             if constexpr (F == kRagged) shift_down(kVec - n, x);
         } else {
 #pragma unroll
-            for (int k = 0; k < kVec; ++k) x[k] = bf16_value(p[tail_index(k, n)]);
+            for (int k = 0; k < kVec; ++k) {
+                x[k] = bf16_value(p[tail_index(k, n)]);
+                __builtin_amdgcn_sched_barrier(0);
+            }
         }
     }
     template <int F, bool NT>
@@ -565,7 +578,9 @@ __device__ __forceinline__ void sync_chunk(const OptParams& o, const Rows& r, fl
                                            float* anchor, int W, int64_t p0, int n, float beta,
                                            float alpha_lr, float inv_w, unsigned flags) {
     static_assert(!EXTRA || WT == 0, "variants run on the run-time-W kernel");
-    constexpr int C = WT > 0 ? (WT < kChunk ? WT : kChunk) : kChunk;
+    // rows of fewer than 4 coordinates take their replicas one at a time
+    constexpr bool kUnroll = WT > 0 && F != kTiny;
+    constexpr int C = F == kTiny ? 1 : WT > 0 ? (WT < kChunk ? WT : kChunk) : kChunk;
     static_assert(WT <= 0 || WT % C == 0, "replica batches must tile W");
     constexpr bool kAdam = O == Opt::ADAMW;
     const int nw = WT > 0 ? WT : W;
@@ -579,12 +594,14 @@ __device__ __forceinline__ void sync_chunk(const OptParams& o, const Rows& r, fl
     // summed in the fixed order i = 0, 1, ..., W-1
     if constexpr (M != Sync::LocalSGD) {
         float acc[kVec] = {0.0f, 0.0f, 0.0f, 0.0f};
-        if constexpr (WT > 0) {
+        if constexpr (kUnroll) {
 #pragma unroll
             for (int i0 = 0; i0 < WT; i0 += C) grad_batch<C, F>(r, i0, p0, n, acc);
         } else {
             int i0 = 0;
-            for (; i0 + C <= nw; i0 += C) grad_batch<C, F>(r, i0, p0, n, acc);
+            if constexpr (C > 1)
+                for (; i0 + C <= nw; i0 += C) grad_batch<C, F>(r, i0, p0, n, acc);
+#pragma nounroll
             for (; i0 < nw; ++i0) grad_batch<1, F>(r, i0, p0, n, acc);
         }
 #pragma unroll
@@ -603,12 +620,14 @@ __device__ __forceinline__ void sync_chunk(const OptParams& o, const Rows& r, fl
     // a sum of differences to a reference that is close to every x_i (the
     // anchor for CPDP, replica 0's x for LocalSGD), so the small deviations
     // keep their precision.
-    if constexpr (WT > 0) {
+    if constexpr (kUnroll) {
 #pragma unroll
         for (int i0 = 0; i0 < WT; i0 += C) step_batch<M, O, C, PS, F>(o, r, i0, p0, n, z, avg_state);
     } else {
         int i0 = 0;
-        for (; i0 + C <= nw; i0 += C) step_batch<M, O, C, PS, F>(o, r, i0, p0, n, z, avg_state);
+        if constexpr (C > 1)
+            for (; i0 + C <= nw; i0 += C) step_batch<M, O, C, PS, F>(o, r, i0, p0, n, z, avg_state);
+#pragma nounroll
         for (; i0 < nw; ++i0) step_batch<M, O, 1, PS, F>(o, r, i0, p0, n, z, avg_state);
     }
     if (avg_state) {
