@@ -172,11 +172,16 @@ struct ParamF32 {
     }
 };
 
+// Both results are computed and one is selected: with an early return for NaN
+// the compiler puts a branch around the values it rounds where the code is large
+// (reconcile of 4 x 16,380 coordinates, bf16 parameters, thread-per-coordinate
+// kernel: 3.3 us with the branches, 2.6 without; of 32 x 1,000,000 all-bf16 ones,
+// split: 90 and 84).
 __device__ __forceinline__ uint32_t bf16_bits(float f) {
-    uint32_t b = __float_as_uint(f);
-    if ((b & 0x7FFFFFFFu) > 0x7F800000u) return (b >> 16) | 0x40u;  // keep NaN quiet
-    b += 0x7FFFu + ((b >> 16) & 1u);                                  // nearest, ties even
-    return b >> 16;
+    const uint32_t b = __float_as_uint(f);
+    const uint32_t quiet = (b >> 16) | 0x40u;                         // a quiet NaN
+    const uint32_t nearest = (b + 0x7FFFu + ((b >> 16) & 1u)) >> 16;  // ties even
+    return (b & 0x7FFFFFFFu) > 0x7F800000u ? quiet : nearest;
 }
 
 __device__ __forceinline__ float bf16_value(uint32_t h) { return __uint_as_float(h << 16); }
