@@ -68,7 +68,7 @@ __global__ __launch_bounds__(kBlock) void sync_plan_kernel(Src src,
 // 4 x 271,117 coordinates in 62 tensors: 14.0 -> 8.3 us; weight decay, 8 x 23.7 M
 // in 161 tensors: 764 -> 726 us, 5.8 TB/s)
 template <Sync M, Opt O, int R, class PS, bool EXTRA, class Src>
-__global__ __launch_bounds__(kSplitThreads) void sync_plan_split_kernel(
+__global__ __launch_bounds__(kSplitThreads, split_waves(R)) void sync_plan_split_kernel(
     Src src, const int64_t* __restrict__ plan, int W, int n, float inv_w, unsigned flags) {
     extern __shared__ __align__(16) float lds[];
     const PlanView v = plan_view(plan, W, n);

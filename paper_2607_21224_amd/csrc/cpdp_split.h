@@ -215,10 +215,15 @@ int launch_split(void (*kernel)(Args...), int64_t blocks, int W, int R, void* st
                                 static_cast<hipStream_t>(stream));
 }
 
+// Wavefronts a SIMD has to hold.  With two replicas a group the block is up to 16
+// wavefronts; AdamW took 66 registers then, which leaves room for one such block
+// a CU where 64 leave room for two (32 x 513,800 coordinates: 107 us, so 87).
+constexpr int split_waves(int R) { return R == 2 ? 8 : 1; }
+
 // ---- flat layout -------------------------------------------------------------------
 
 template <Sync M, Opt O, int R, class PS, bool EXTRA, class GS, class MS, class Src>
-__global__ __launch_bounds__(kSplitThreads) void sync_split_kernel(
+__global__ __launch_bounds__(kSplitThreads, split_waves(R)) void sync_split_kernel(
     Src src, typename PS::T* __restrict__ params, typename MS::T* __restrict__ mom,
     float* __restrict__ mom2, GradPtr<EXTRA, GS> __restrict__ grads, float* __restrict__ slow,
     float* __restrict__ anchor, int W, int64_t ld, int64_t P, float inv_w, unsigned flags) {

@@ -16,6 +16,8 @@ namespace cpdp { namespace {
 template int sync_w<Sync::CPDP, Opt::SGD, 0, ParamF32>(const OptParams&, const SyncArgs&);
 template int sync_w<Sync::CPDP, Opt::ADAMW, 0, ParamF32>(const OptParams&, const SyncArgs&);
 template int sync_w<Sync::CPDP, Opt::SGD, 16, ParamF32>(const OptParams&, const SyncArgs&);
+template int sync_split<Sync::CPDP, Opt::ADAMW, ParamF32, false, ParamF32, ParamF32, DirectScalars>(
+    const DirectScalars&, const SyncArgs&);
 } }
 """
 
@@ -58,3 +60,10 @@ def test_wavefronts_of_the_thread_per_coordinate_kernel(usage, opt, wt, waves):
     vgprs, occupancy, scratch = _kernel(usage, "11sync_kernel", opt, wt)
     assert scratch == 0
     assert occupancy >= waves, f"{vgprs} registers: {occupancy} wavefronts a SIMD"
+
+
+def test_two_split_blocks_a_cu(usage):
+    """AdamW above 16 replicas: two replicas a group, 16 wavefronts a block, and
+    a CU holds 32 wavefronts."""
+    vgprs, occupancy, scratch = _kernel(usage, "17sync_split_kernel", "OptE2", "ELi2E")
+    assert scratch == 0 and occupancy == 8, f"{vgprs} registers: {occupancy} wavefronts a SIMD"
