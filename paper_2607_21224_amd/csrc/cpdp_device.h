@@ -481,7 +481,7 @@ __device__ __forceinline__ void local_dispatch(const Src& src, typename PS::T* p
 // ---- fused synchronisation steps ----------------------------------------------
 //
 // One thread owns 4 coordinates across all W replicas.  WT > 0 fixes W at
-// compile time (fully unrolled); WT == 0 takes W at run time (batches of
+// compile time (fully unrolled); otherwise W is taken at run time (batches of
 // kChunk, then single replicas).  Within a batch all loads are issued before
 // any store.  The batching matters because the compiler cannot prove that two
 // replica rows never alias (ld is a run-time value, plan pointers are data),
@@ -582,7 +582,7 @@ template <Sync M, Opt O, int WT, class PS, int F, bool EXTRA, class Rows>
 __device__ __forceinline__ void sync_chunk(const OptParams& o, const Rows& r, float* slow,
                                            float* anchor, int W, int64_t p0, int n, float beta,
                                            float alpha_lr, float inv_w, unsigned flags) {
-    static_assert(!EXTRA || WT == 0, "variants run on the run-time-W kernel");
+    static_assert(!EXTRA || WT <= 0, "variants run on the run-time-W kernel");
     // rows of fewer than 4 coordinates take their replicas one at a time
     constexpr bool kUnroll = WT > 0 && F != kTiny;
     constexpr int C = F == kTiny ? 1 : WT > 0 ? (WT < kChunk ? WT : kChunk) : kChunk;
@@ -627,7 +627,8 @@ __device__ __forceinline__ void sync_chunk(const OptParams& o, const Rows& r, fl
     // keep their precision.
     if constexpr (kUnroll) {
 #pragma unroll
-        for (int i0 = 0; i0 < WT; i0 += C) step_batch<M, O, C, PS, F>(o, r, i0, p0, n, z, avg_state);
+        for (int i0 = 0; i0 < WT; i0 += C)
+            step_batch<M, O, C, PS, F>(o, r, i0, p0, n, z, avg_state);
     } else {
         int i0 = 0;
         if constexpr (C > 1)
@@ -670,24 +671,41 @@ using GradPtr = typename std::conditional<EXTRA, typename GS::T*, const typename
 
 // ---- launch helpers -------------------------------------------------------------
 
-inline int64_t blocks_for(int64_t P) { return (P + (int64_t)kBlock * kVec - 1) / ((int64_t)kBlock * kVec); }
+inline int64_t blocks_for(int64_t P) {
+    return (P + (int64_t)kBlock * kVec - 1) / ((int64_t)kBlock * kVec);
+}
 
 template <class T>
 struct same_type {
     using type = T;
 };
 
+// LDS that a block of kBlock threads reserves so that at most `waves` wavefronts a
+// SIMD are resident (0: as many as fit): a CU has 160 KB, handed out in units of
+// 1280 bytes, and a block may ask for 64 KB.
+constexpr size_t lds_for_waves(int waves) {
+    if (waves == 0) return 0;
+    const size_t share = (size_t)160 * 1024 * (kBlock / 64) / (4 * waves) / 1280 * 1280;
+    return share < 65536 ? share : 65536;
+}
+
 // Argument types come from the kernel's signature only (the trailing
 // parameters are a non-deduced context), so every argument is converted to
 // exactly what the kernel takes before its address goes into argv.
 template <class... Args>
-int launch(void (*kernel)(Args...), int64_t blocks, void* stream,
-           typename same_type<Args>::type... args) {
+int launch_resident(int waves, void (*kernel)(Args...), int64_t blocks, void* stream,
+                    typename same_type<Args>::type... args) {
     void* argv[] = {static_cast<void*>(&args)...};
     hipError_t e = hipLaunchKernel(reinterpret_cast<const void*>(kernel),
-                                   dim3((unsigned)blocks), dim3(kBlock), argv, 0,
-                                   static_cast<hipStream_t>(stream));
+                                   dim3((unsigned)blocks), dim3(kBlock), argv,
+                                   lds_for_waves(waves), static_cast<hipStream_t>(stream));
     return (int)e;
+}
+
+template <class... Args>
+int launch(void (*kernel)(Args...), int64_t blocks, void* stream,
+           typename same_type<Args>::type... args) {
+    return launch_resident(0, kernel, blocks, stream, args...);
 }
 
 struct SyncArgs {

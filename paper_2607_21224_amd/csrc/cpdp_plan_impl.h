@@ -106,7 +106,7 @@ int sync_plan_t(Src src, const int64_t* plan, int W, int n, int64_t total_chunks
                 unsigned flags, void* stream) {
     const float inv_w = 1.0f / (float)W;
     if (can_split(W, total_chunks, kBlock))
-        return with_split_r<PS>(W, [&](auto R) {
+        return with_split_r<O, PS>(W, [&](auto R) {
             return flags != 0 ? launch_split(sync_plan_split_kernel<M, O, R, PS, true, Src>,
                                              total_chunks, W, R, stream, src, plan, W, n, inv_w,
                                              flags)

@@ -194,15 +194,21 @@ __device__ __forceinline__ void split_dispatch(const Src& src, const Rows& r, fl
         split_chunk<M, O, R, PS, kTiny, EXTRA>(src, r, slow, anchor, W, q0, P, inv_w, flags, lds);
 }
 
-// Replicas a group holds: one up to 16, then two, or four where the
-// parameters are bf16 and a row is half as long (W = 32, all rows bf16, 1.0 M
-// coordinates: 65 us with four, 72 with two; with fp32 rows 196 against 189 at
-// 1.6 M).
-template <class PS, class Launch>
+// The step as the dispatch rules see it.
+template <Sync M, Opt O, class PS, class MS = ParamF32>
+constexpr StepKind step_kind() {
+    return {M, O, std::is_same<PS, ParamBF16>::value, std::is_same<MS, ParamBF16>::value};
+}
+
+// Replicas a group holds: one up to 16 groups, then two, or four where the
+// parameters are bf16 and a row is half as long (all-bf16 DDP, 32 x 262,140: 24 us
+// with four, 27 with two).  AdamW takes two all the same (24 x 2.7 M, bf16
+// parameters: 324 us with two, 349 with four).
+template <Opt O, class PS, class Launch>
 int with_split_r(int W, Launch launch_r) {
     if (W <= kSplitGroups) return launch_r(std::integral_constant<int, 1>());
-    constexpr int kMany = std::is_same<PS, ParamBF16>::value ? 4 : 2;
-    return launch_r(std::integral_constant<int, kMany>());
+    constexpr bool kFour = std::is_same<PS, ParamBF16>::value && O != Opt::ADAMW;
+    return launch_r(std::integral_constant<int, kFour ? 4 : 2>());
 }
 
 template <class... Args>
@@ -242,7 +248,7 @@ int sync_split(const Src& src, const SyncArgs& a) {
     // mutable (flags != 0), so dropping const here restores the caller's type
     const GradPtr<EXTRA, GS> grads =
         const_cast<typename GS::T*>(static_cast<const typename GS::T*>(a.grads));
-    return with_split_r<PS>(a.W, [&](auto R) {
+    return with_split_r<O, PS>(a.W, [&](auto R) {
         return launch_split(sync_split_kernel<M, O, R, PS, EXTRA, GS, MS, Src>, blocks_for(a.P),
                             a.W, R, a.stream, src, static_cast<T*>(a.params),
                             static_cast<typename MS::T*>(a.mom), a.mom2, grads, a.slow, a.anchor,

@@ -1,7 +1,8 @@
 // The flat-layout synchronisation kernels (CPDP reconcile, LocalSGD averaging,
 // DDP gradient step) and their dispatch over update rule, parameter,
-// gradient and momentum storage types, and W.  Each strategy is instantiated in a translation unit of its own
-// (kernels_sync_<strategy>.hip) so the three compile in parallel.
+// gradient and momentum storage types, and W.  Each strategy is instantiated in
+// a translation unit of its own (kernels_sync_<strategy>.hip) so the three
+// compile in parallel.
 #pragma once
 
 #include "cpdp_device.h"
@@ -10,8 +11,16 @@
 namespace cpdp {
 namespace {
 
+// WT: replicas at compile time; 0: at run time; kManyW: at run time, more than the
+// split step takes.  AdamW's long update on that many replicas is faster with two
+// wavefronts a SIMD that keep more of a batch in registers than with four (40 x
+// 100,000 fp32 coordinates: 37.7 us with four, 33.9 with two; 3.0 M level).
+constexpr int kManyW = -1;
+constexpr int column_waves_max(Opt O, int WT) { return O == Opt::ADAMW && WT == kManyW ? 2 : 8; }
+
 template <Sync M, Opt O, int WT, class PS, bool EXTRA, class GS, class MS>
-__global__ __launch_bounds__(kBlock) void sync_kernel(
+__global__ __launch_bounds__(kBlock)
+__attribute__((amdgpu_waves_per_eu(1, column_waves_max(O, WT)))) void sync_kernel(
     OptParams o, typename PS::T* __restrict__ params, typename MS::T* __restrict__ mom,
     float* __restrict__ mom2, GradPtr<EXTRA, GS> __restrict__ grads, float* __restrict__ slow,
     float* __restrict__ anchor, int W, int64_t ld, int64_t P, float beta, float alpha_lr,
@@ -29,7 +38,7 @@ __global__ __launch_bounds__(kBlock) void sync_kernel(
 
 template <Sync M, Opt O, int WT, class PS, bool EXTRA = false, class GS = ParamF32,
           class MS = ParamF32>
-int sync_w(const OptParams& o, const SyncArgs& a) {
+int sync_w(const OptParams& o, const SyncArgs& a, int resident = 0) {
     using T = typename PS::T;
     const float alpha_lr = a.alpha * o.lr;
     const float inv_w = 1.0f / (float)a.W;
@@ -37,56 +46,37 @@ int sync_w(const OptParams& o, const SyncArgs& a) {
     // mutable (flags != 0), so dropping const here restores the caller's type
     const GradPtr<EXTRA, GS> grads =
         const_cast<typename GS::T*>(static_cast<const typename GS::T*>(a.grads));
-    return launch(sync_kernel<M, O, WT, PS, EXTRA, GS, MS>, blocks_for(a.P), a.stream, o,
-                  static_cast<T*>(a.params), static_cast<typename MS::T*>(a.mom), a.mom2, grads,
-                  a.slow, a.anchor, a.W, a.ld, a.P, a.beta, alpha_lr, inv_w, a.flags);
+    return launch_resident(resident, sync_kernel<M, O, WT, PS, EXTRA, GS, MS>, blocks_for(a.P),
+                           a.stream, o, static_cast<T*>(a.params),
+                           static_cast<typename MS::T*>(a.mom), a.mom2, grads, a.slow, a.anchor,
+                           a.W, a.ld, a.P, a.beta, alpha_lr, inv_w, a.flags);
 }
 
-// Which kernel takes the step.  The split one, except
-//  * W outside its range (W = 1 and 2, and more than 32 replicas), or so many
-//    coordinates that its blocks of up to 1024 threads pass the 2^32 work items
-//    of a launch (W * P >= 2^34 up to 16 replicas);
-//  * fp32 momentum SGD on 4, 8 or 16 replicas when the rows stay in the 256 MB
-//    last-level cache from one call to the next and the thread-per-coordinate
-//    kernel has a wavefront for every SIMD (1024 of them): the blocks of the
-//    split kernel then run in a few rounds that load and store in step, and
-//    that kernel is 3-17 % faster (W = 8, 262,144 coordinates: 7.7 against
-//    8.2 us; W = 16: 13.2 against 16.0).  With fewer wavefronts its serial
-//    batches cost more (W = 8, 65,539: 4.3 against 3.9), and past the cache
-//    the split kernel streams faster (W = 16, 800,001: 52.6 against 46.3);
-//  * a DDP step that writes the gradient mean back, past the cache: it streams
-//    as many rows in as out and the two are level to 2 % in favour of the
-//    thread-per-coordinate kernel (W = 6, 11.2 M: 290 against 296 us); on a
-//    small state the split one is twice as fast.
-constexpr int64_t kCachedElems = (int64_t)1 << 23;  // W * P: 168 MB of fp32 momentum SGD rows
-
-template <Sync M, Opt O, class PS, class GS, class MS>
-constexpr bool kPlainRows = O != Opt::ADAMW && std::is_same<PS, ParamF32>::value &&
-                            std::is_same<GS, ParamF32>::value && std::is_same<MS, ParamF32>::value;
-
+// Which kernel takes the step (the rules and what they were measured at are in
+// cpdp_dispatch.h).
 template <Sync M, Opt O, class PS, class GS = ParamF32, class MS = ParamF32>
 int sync_t(const OptParams& o, const SyncArgs& a) {
-    constexpr bool plain = kPlainRows<M, O, PS, GS, MS>;
+    constexpr StepKind kind = step_kind<M, O, PS, MS>();
+    const int mean_waves = ddp_mean_waves(kind, a.W, a.P, a.flags & kSyncWriteGbar);
+    const bool split = can_split(a.W, blocks_for(a.P), kBlock) && mean_waves == 0 &&
+                       !takes_columns(kind, a.W, a.P, a.flags != 0);
     const DirectScalars src{o, a.beta, a.alpha * o.lr};
-    const bool cached = a.P < kCachedElems / a.W;
-    const bool splits = can_split(a.W, blocks_for(a.P), kBlock);
     if constexpr (std::is_same<GS, ParamF32>::value && std::is_same<MS, ParamF32>::value) {
-        if (a.flags != 0) {
-            const bool split = M != Sync::DDP || !(a.flags & kSyncWriteGbar) || cached;
-            return splits && split ? sync_split<M, O, PS, true, GS, MS>(src, a)
-                                           : sync_w<M, O, 0, PS, true>(o, a);
-        }
+        if (a.flags != 0)
+            return split ? sync_split<M, O, PS, true, GS, MS>(src, a)
+                         : sync_w<M, O, 0, PS, true>(o, a, mean_waves);
     }
+    if (split) return sync_split<M, O, PS, false, GS, MS>(src, a);
     if (a.W == 1) return sync_w<M, O, 1, PS, false, GS, MS>(o, a);
     if (a.W == 2) return sync_w<M, O, 2, PS, false, GS, MS>(o, a);
-    if constexpr (plain) {
-        if (cached && blocks_for(a.P) >= 1024) {
-            if (a.W == 4) return sync_w<M, O, 4, PS, false, GS, MS>(o, a);
-            if (a.W == 8) return sync_w<M, O, 8, PS, false, GS, MS>(o, a);
-            if (a.W == 16) return sync_w<M, O, 16, PS, false, GS, MS>(o, a);
-        }
+    if constexpr (fixed_w(kind, 4))
+        if (a.W == 4) return sync_w<M, O, 4, PS, false, GS, MS>(o, a);
+    if constexpr (fixed_w(kind, 8)) {
+        if (a.W == 8) return sync_w<M, O, 8, PS, false, GS, MS>(o, a);
+        if (a.W == 16) return sync_w<M, O, 16, PS, false, GS, MS>(o, a);
     }
-    if (splits) return sync_split<M, O, PS, false, GS, MS>(src, a);
+    if constexpr (O == Opt::ADAMW)
+        if (a.W > split_max_w(kBlock)) return sync_w<M, O, kManyW, PS, false, GS, MS>(o, a);
     return sync_w<M, O, 0, PS, false, GS, MS>(o, a);
 }
 

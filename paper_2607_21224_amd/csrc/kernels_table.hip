@@ -108,7 +108,8 @@ template <Sync M, Opt O, class PS>
 int sync_table_t(const TableScalars& src, const SyncArgs& a) {
     using T = typename PS::T;
     const float inv_w = 1.0f / (float)a.W;
-    if (can_split(a.W, blocks_for(a.P), kBlock)) {
+    if (can_split(a.W, blocks_for(a.P), kBlock) &&
+        !takes_columns(step_kind<M, O, PS>(), a.W, a.P, true)) {
         return a.flags != 0 ? sync_split<M, O, PS, true, ParamF32, ParamF32>(src, a)
                             : sync_split<M, O, PS, false, ParamF32, ParamF32>(src, a);
     }

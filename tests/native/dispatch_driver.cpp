@@ -49,6 +49,45 @@ int main() {
     CHECK(can_split(16, ((int64_t)1 << 30) / 256 - 1, 64), 16, (int64_t)1 << 30);
     CHECK(launch_fits(((int64_t)1 << 30) / 256, 64), 16, (int64_t)1 << 30);
     CHECK(launch_fits(((int64_t)1 << 31) / 256, 64), 8, (int64_t)1 << 31);
+    // the rules between the two kernels: what has nothing to split is never
+    // weighed, sizes far on either side go to the split step whatever the types
+    // are, and every line is a single one (no gaps between a kernel's sizes
+    // other than where whole vectors end)
+    for (Sync m : {Sync::CPDP, Sync::LocalSGD, Sync::DDP})
+        for (Opt o : {Opt::SGD, Opt::SGD_WD, Opt::ADAMW})
+            for (int types = 0; types < 4; ++types)
+                for (int W = kSplitMinW; W <= 32; ++W) {
+                    const StepKind k{m, o, (types & 1) != 0, (types & 2) != 0};
+                    const bool none = column_last(k, W) == INT64_MAX;
+                    CHECK(none == (types == 3 && (m == Sync::CPDP ? W > 8 : W > 16 && W <= 24)),
+                          W, types);
+                    int turns = 0;
+                    bool before = false;
+                    for (int64_t waves = 1; waves < 20000; ++waves) {
+                        const bool column = takes_columns(k, W, waves * 256 - 1, true);
+                        if (column) {
+                            CHECK(waves >= 640 && W * waves > 8192, W, waves);
+                            CHECK(none || waves <= 8192, W, waves);
+                        }
+                        turns += column != before;
+                        before = column;
+                        // ragged rows of a compile-time-W kernel: from a wavefront a SIMD on
+                        if (waves < 640) CHECK(!takes_columns(k, W, waves * 256 - 1, false), W, waves);
+                        if (o == Opt::ADAMW)
+                            CHECK(takes_columns(k, W, waves * 256, true) ==
+                                      takes_columns(k, W, waves * 256, false), W, waves);
+                    }
+                    CHECK(turns <= 2, W, turns);
+                    if (!none) CHECK(!takes_columns(k, W, (int64_t)1 << 33, false), W, types);
+                    CHECK(ddp_mean_waves(k, W, 1 << 20, true) == 0 || W > 8, W, types);
+                    CHECK(ddp_mean_waves(k, W, 1 << 23, false) == 0, W, types);
+                    CHECK((ddp_mean_waves(k, W, 1 << 23, true) != 0) ==
+                              (m == Sync::DDP && W <= 6), W, types);
+                    if (o == Opt::ADAMW) CHECK(!fixed_w(k, W), W, types);
+                    // rows of whole vectors only, and never the ragged ones beside them
+                    CHECK(takes_columns({Sync::CPDP, Opt::SGD, false, false}, 8, 4096, false), 8, 4096);
+                    CHECK(!takes_columns({Sync::CPDP, Opt::SGD, false, false}, 8, 4097, false), 8, 4097);
+                }
     std::printf("%s\n", failures ? "FAILED" : "OK");
     return failures ? 1 : 0;
 }
