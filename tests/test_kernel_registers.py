@@ -13,9 +13,9 @@ from paper_2607_21224_amd import build
 UNIT = """
 #include "cpdp_sync_impl.h"
 namespace cpdp { namespace {
-template int sync_w<Sync::CPDP, Opt::SGD, 0, ParamF32>(const OptParams&, const SyncArgs&);
-template int sync_w<Sync::CPDP, Opt::ADAMW, 0, ParamF32>(const OptParams&, const SyncArgs&);
-template int sync_w<Sync::CPDP, Opt::SGD, 16, ParamF32>(const OptParams&, const SyncArgs&);
+template int sync_w<Sync::CPDP, Opt::SGD, 0, ParamF32>(const OptParams&, const SyncArgs&, int);
+template int sync_w<Sync::CPDP, Opt::ADAMW, 0, ParamF32>(const OptParams&, const SyncArgs&, int);
+template int sync_w<Sync::CPDP, Opt::SGD, 16, ParamF32>(const OptParams&, const SyncArgs&, int);
 template int sync_split<Sync::CPDP, Opt::ADAMW, ParamF32, false, ParamF32, ParamF32, DirectScalars>(
     const DirectScalars&, const SyncArgs&);
 } }
