@@ -144,4 +144,14 @@ constexpr int ddp_mean_waves(const StepKind& k, int W, int64_t P, bool writes_me
     return P < ((int64_t)1 << 23) / W ? 0 : W == 3 ? 3 : 2;
 }
 
+// Wavefronts a SIMD that a step-table step on one and two replicas keeps resident
+// (0: as many as fit).  Its run-time-W kernel has room for six, which small and
+// mid-sized states are faster with (2 x 1,141,054 DDP: 9.3 us, 10.5 with three)
+// and large ones slower (2 x 16.9 M CPDP 157 and 149, 2 x 15.1 M LocalSGD 110 and
+// 106).  DDP on one replica, three rows in all, keeps the six (19.7 M: 63 and 69).
+constexpr int table_waves(const StepKind& k, int W, int64_t P) {
+    if (k.mode == Sync::DDP && W == 1) return 0;
+    return W < kSplitMinW && P >= ((int64_t)1 << 24) / W ? 3 : 0;
+}
+
 }  // namespace cpdp

@@ -43,7 +43,6 @@ __device__ __forceinline__ void local_steps_chunk(const int64_t* table, int64_t 
     PS::template store<F, kNTS>(params + at, n, th);
 }
 
-// No __restrict__: it would let the compiler move the data loads past the table's.
 template <Opt O, class PS>
 __global__ __launch_bounds__(kBlock) void local_steps_table_kernel(
     const int64_t* table, int64_t ahead, typename PS::T* params, float* mom, float* mom2,
@@ -115,15 +114,16 @@ int sync_table_t(const TableScalars& src, const SyncArgs& a) {
     }
     // step tables take fp32 gradients
     const float* grads = static_cast<const float*>(a.grads);
+    const int resident = table_waves(step_kind<M, O, PS>(), a.W, a.P);
     if (a.flags != 0)
-        return launch(sync_table_kernel<M, O, PS, true>, blocks_for(a.P), a.stream, src.table, src.ahead,
-                      static_cast<T*>(a.params), static_cast<float*>(a.mom), a.mom2,
-                      const_cast<float*>(grads),
-                      a.slow, a.anchor, a.W, a.ld, a.P, inv_w, a.flags);
-    return launch(sync_table_kernel<M, O, PS, false>, blocks_for(a.P), a.stream, src.table, src.ahead,
-                  static_cast<T*>(a.params), static_cast<float*>(a.mom), a.mom2, grads, a.slow,
-                  a.anchor, a.W,
-                  a.ld, a.P, inv_w, a.flags);
+        return launch_resident(resident, sync_table_kernel<M, O, PS, true>, blocks_for(a.P),
+                               a.stream, src.table, src.ahead, static_cast<T*>(a.params),
+                               static_cast<float*>(a.mom), a.mom2, const_cast<float*>(grads),
+                               a.slow, a.anchor, a.W, a.ld, a.P, inv_w, a.flags);
+    return launch_resident(resident, sync_table_kernel<M, O, PS, false>, blocks_for(a.P),
+                           a.stream, src.table, src.ahead, static_cast<T*>(a.params),
+                           static_cast<float*>(a.mom), a.mom2, grads, a.slow, a.anchor, a.W, a.ld,
+                           a.P, inv_w, a.flags);
 }
 
 template <Sync M, Opt O>

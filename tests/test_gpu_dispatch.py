@@ -119,7 +119,8 @@ def test_rows_of_whole_vectors(P, W, types, method):
 
 @pytest.mark.parametrize("flags", [0, 3])
 @pytest.mark.parametrize("W,P", [(17, 515), (30, 1023), (32, 260), (12, 1100 * 256 + 5),
-                                 (4, 4096), (32, 3), (40, 259)])
+                                 (4, 4096), (32, 3), (40, 259),
+                                 (2, (1 << 23) + 5)])
 @pytest.mark.parametrize("opt,param,method", [("sgd", "bf16", "cpdp"), ("adamw", "f32", "localsgd"),
                                               ("sgd_wd", "f32", "ddp"), ("adamw", "bf16", "cpdp")])
 def test_tables_and_plans_equal_flat_steps(W, P, opt, param, method, flags):
