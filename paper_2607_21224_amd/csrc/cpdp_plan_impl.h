@@ -9,7 +9,23 @@
 namespace cpdp {
 namespace {
 
-constexpr unsigned kWaveSearchBlocks = 6144;
+// Which search finds a block's tensor in the local step and in the
+// thread-per-coordinate synchronisation step.  While every SIMD has at most two
+// wavefronts, each block's chain of loads is the time, and one 64-lane load is
+// shorter than log2(n) scalar ones from 5 on (30 tensors, 585 blocks: local step
+// 2.70 us by the wavefront, 2.87 by the scalar search; synchronisation step of one
+// replica 3.82, 3.99) and longer than 2 (4 tensors: 2.65, 2.61; 3.72, 3.69).
+// With more blocks they hide each other's chain and the wide loads get in the way
+// of the data's (2,490 blocks, 4 tensors, a state that is not in the cache: 4.49,
+// 3.92; 6.63, 5.72), but with a large table the scalar search waits longer up to
+// 6144 (600 tensors, 4,700 blocks: 7.2, 8.3; 10.5, 11.3; local
+// step of 4 replicas of 120 tensors, 2,260 blocks: 4.71, 5.33).
+// The split step, whose groups all search, is level or faster with the wavefront's.
+__device__ __forceinline__ int64_t plan_tensor_by_size(const PlanView& v, int W, int n,
+                                                       int64_t b) {
+    const unsigned most = (int64_t)W * n > 256 ? 6144 : 2048;
+    return n > 8 && gridDim.x <= most ? plan_tensor(v, n, b) : plan_tensor_scalar(v, n, b);
+}
 
 // cell (row, chunk b), in the local step's block order -> replica row, tensor t,
 // its chunk
@@ -23,13 +39,7 @@ __global__ __launch_bounds__(kBlock) void local_step_plan_kernel(Src src,
     const PlanView v = plan_view(plan, W, n);
     const int64_t row = cell / total_chunks;
     const int64_t b = cell - row * total_chunks;
-    // Which search: while the launch is about one round of wavefronts, each
-    // block's chain of loads is the time; beyond, other blocks hide it and the
-    // 64-lane loads cost more than they save (local SGD step of 4 x 50,001
-    // coordinates in 200 tensors, 4 x 271,117 in 62 and 2 x 1,000,001 in 100:
-    // 3.4, 5.3 and 8.6 us by the wavefront, 3.9, 5.6 and 8.1 by the scalar search)
-    const int64_t t = gridDim.x <= kWaveSearchBlocks ? plan_tensor(v, n, b)
-                                                     : plan_tensor_scalar(v, n, b);
+    const int64_t t = plan_tensor_by_size(v, W, n, b);
     // the tensor's size and its four addresses come in one round trip: behind
     // the test of p0 the addresses would take a second one
     const int64_t k = row * n + t;
@@ -49,7 +59,7 @@ __global__ __launch_bounds__(kBlock) void sync_plan_kernel(Src src,
                                                            int n, float inv_w, unsigned flags) {
     const PlanView v = plan_view(plan, W, n);
     const int64_t b = blockIdx.x;
-    const int64_t t = plan_tensor(v, n, b);
+    const int64_t t = plan_tensor_by_size(v, W, n, b);
     const int64_t P = v.numel[t];
     const int64_t p0 = ((b - v.chunk_start[t]) * kBlock + threadIdx.x) * kVec;
     if (p0 >= P) return;

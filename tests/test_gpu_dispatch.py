@@ -153,3 +153,37 @@ def test_tables_and_plans_equal_flat_steps(W, P, opt, param, method, flags):
             assert torch.equal(multi.gather(k, i), rows[i, :P]), ("plan", W, P, k, i)
     assert torch.equal(multi.gather("anchor"), st.anchor) and \
         torch.equal(multi.gather("slow_mom"), st.slow_mom)
+
+
+@pytest.mark.parametrize("W,n,blocks", [(1, 1, 3), (1, 8, 40), (1, 9, 40), (2, 9, 2048),
+                                        (1, 9, 2049), (1, 256, 2049), (2, 129, 2049),
+                                        (1, 257, 6144), (1, 257, 6145), (33, 10, 660)])
+@pytest.mark.parametrize("kind", ["local", "sync"])
+def test_plan_blocks_find_their_tensors(W, n, blocks, kind):
+    """Both searches of a plan, on each side of the lines between them: `blocks`
+    blocks over n tensors of 1 to 3 chunks, the last with the rest."""
+    chunks = blocks // W if kind == "local" else blocks
+    sizes = [(1 + i % 3) * 256 - i % 5 for i in range(n)]
+    sizes[-1] = 3
+    sizes[-1] += (chunks - sum((s + 255) // 256 for s in sizes)) * 256
+    assert sizes[-1] > 0
+    P = sum(sizes)
+    st, grads = _state(W, P)
+    multi = CpdpMultiState(W, sizes)
+    for k, rows in _rows(st, grads).items():
+        for i in range(W):
+            for dst, src in zip(getattr(multi, k)[i], rows[i, :P].split(sizes)):
+                dst[:len(src)] = src
+    for k in ("anchor", "slow_mom"):
+        for dst, src in zip(getattr(multi, k), getattr(st, k).split(sizes)):
+            dst[:len(src)] = src
+    multi.opt_step = st.opt_step
+    st.K = multi.K = 2 if kind == "local" else 1
+    assert st.step_opt(1, grads, OPTS["sgd"], BETA, ALPHA) == \
+        multi.step(1, OPTS["sgd"], BETA, ALPHA) == ("local" if kind == "local" else "reconcile")
+    torch.cuda.synchronize()
+    for k, rows in _rows(st, grads).items():
+        for i in range(W):
+            assert torch.equal(multi.gather(k, i), rows[i, :P]), (W, n, blocks, kind, k, i)
+    assert torch.equal(multi.gather("anchor"), st.anchor)
+    assert torch.equal(multi.gather("slow_mom"), st.slow_mom)
