@@ -83,3 +83,32 @@ def test_capture_before_the_table_is_refilled():
     assert table.position() == K
     for x, y in zip(_bits(a), _bits(b)):
         assert torch.equal(x, y)
+
+
+@pytest.mark.parametrize("flags", [1, 2, 3])
+@pytest.mark.parametrize("kind,param,method,W,P,K", [
+    ("adamw", "f32", "cpdp", 4, 515, 3), ("sgd", "bf16", "ddp", 17, 260, 2),
+    ("sgd_wd", "f32", "localsgd", 32, 1023, 4)])
+def test_captured_variants_equal_single_steps(kind, param, method, W, P, K, flags):
+    """The synchronisation variants inside a captured run.  One step writes its
+    gradient rows, so every step has rows of its own on both sides."""
+    dt = torch.bfloat16 if param == "bf16" else torch.float32
+    gen = torch.Generator(device="cuda").manual_seed(11)
+    theta = (torch.randn(P, generator=gen, device="cuda") * 0.02).to(dt)
+    a, b = (CpdpState(W, P, K=K, param_dt=param, adamw=kind == "adamw") for _ in range(2))
+    for st in (a, b):
+        st.init_opt(theta, _opt(kind, 0))
+    grads = [torch.zeros((W, a.ld), device="cuda") for _ in range(K)]
+    for g in grads:
+        g[:, :P] = torch.randn((W, P), generator=gen, device="cuda") * 1e-3
+    single = [g.clone() for g in grads]
+    table = StepTable([(_opt(kind, s), s + 1, 0.5, 0.75) for s in range(2 * K)])
+    graph, _ = b.capture_steps(grads, table, method=method, flags=flags)
+    for period in range(2):
+        graph.replay()
+        for j in range(K):
+            a.step_opt(j + 1, single[j], _opt(kind, period * K + j), 0.5, 0.75, method=method,
+                       flags=flags)
+        torch.cuda.synchronize()
+        for x, y in zip(_bits(a) + single, _bits(b) + grads):
+            assert torch.equal(x, y), (kind, param, method, flags, period)
