@@ -546,8 +546,9 @@ def main() -> int:
     # traffic-shape ceiling: the synchronisation kernel's exact rows streamed
     # with no arithmetic (in place, the state keeps its bits), in two orders:
     # each batch of 8 rows written back right after it is read, and the
-    # library's own order.  The ceiling is the faster, each order timed as the
-    # best of three batches of launches.
+    # library's thread-per-coordinate kernel's ("library_order").  The ceiling is
+    # the faster, each order timed as the best of three batches of launches.  The
+    # split kernel, which issues a block's loads all at once, can lie above it.
     shape = None
     if multi is None:
         from synth.device import SYNC_ORDER_W, ShapePass, ShapeSyncPass
@@ -710,7 +711,8 @@ def main() -> int:
         "shape_ceiling": None if shape is None else {
             "GB_per_s": round(shape["GBps"], 1), "ms": round(shape["ms"], 5),
             "kernel": "synth shape kernels: the same rows, loads and in-place stores, no "
-                      "arithmetic, in two orders (the faster one is the ceiling)",
+                      "arithmetic, in two orders (the faster one is the ceiling); library_order "
+                      "is the thread-per-coordinate kernel's, which the split step can beat",
             "order": shape["order"], "orders_GB_per_s": shape["orders_GBps"],
             "rows": shape["rows"]},
         "wall_s_timed_region": round(wall, 4),

@@ -313,8 +313,8 @@ def cpdp_reconcile(params, mom, grads, slow_mom, anchor, W, P, ld, K, lr, mu,
                            _span(mom, n, mom_dt, "mom"),
                            _span(grads, n, grad_dt, "grads"),
                            _span(slow_mom, P, CPDP_F32, "slow_mom"),
-                           _span(anchor, P, CPDP_F32, "anchor"), W, P, ld, int(K), float(lr), float(mu), float(beta),
-                           float(alpha), _dt(param_dt), _dt(grad_dt),
+                           _span(anchor, P, CPDP_F32, "anchor"), W, P, ld, int(K),
+                           float(lr), float(mu), float(beta), float(alpha), _dt(param_dt), _dt(grad_dt),
                            _dt(mom_dt), _stream(stream))
     return _done(s, "cpdp_reconcile", check)
 

@@ -651,10 +651,10 @@ int cpdp_sync_step_plan(int strategy, const cpdp_plan* plan, int K, const cpdp_o
     if (kind == cpdp::Opt::ADAMW && !plan->has_mom2) return CPDP_ERR_NULL;
     if (int s = check_seal(plan)) return s;
     if (plan->total_chunks == 0) return CPDP_OK;
-    return hip_status(cpdp::launch_sync_plan(sync_mode(strategy), kind, o, param_kind(plan->param_dt),
-                                             static_cast<const int64_t*>(plan->table), plan->W,
-                                             plan->n_tensors, plan->total_chunks, beta, alpha,
-                                             flags, stream));
+    return hip_status(cpdp::launch_sync_plan(
+        sync_mode(strategy), kind, o, param_kind(plan->param_dt),
+        static_cast<const int64_t*>(plan->table), plan->W, plan->n_tensors, plan->total_chunks,
+        beta, alpha, flags, stream));
 }
 
 int64_t cpdp_step_table_bytes(int n_steps) {
@@ -859,11 +859,13 @@ float cpdp_lr_at(int64_t step, int64_t total_steps, int64_t warmup_steps, float 
     if (!(finite(base_lr) && base_lr > 0.0f && finite(min_lr) && min_lr >= 0.0f &&
           min_lr <= base_lr))
         return nan;
-    if (step < warmup_steps) return (float)((double)base_lr * (double)(step + 1) / (double)warmup_steps);
+    if (step < warmup_steps)
+        return (float)((double)base_lr * (double)(step + 1) / (double)warmup_steps);
     const double span = (double)std::max<int64_t>(1, total_steps - warmup_steps);
     const double frac = (double)(step - warmup_steps) / span;
     const double pi = 3.14159265358979323846;
-    return (float)((double)min_lr + ((double)base_lr - (double)min_lr) * 0.5 * (1.0 + std::cos(pi * frac)));
+    return (float)((double)min_lr +
+                   ((double)base_lr - (double)min_lr) * 0.5 * (1.0 + std::cos(pi * frac)));
 }
 
 float cpdp_linear_scaled_lr(float base_lr, int64_t base_batch, int64_t global_batch) {
@@ -875,9 +877,11 @@ float cpdp_linear_scaled_lr(float base_lr, int64_t base_batch, int64_t global_ba
 const char* cpdp_status_str(int status) {
     switch (status) {
         case CPDP_OK: return "CPDP_OK";
-        case CPDP_ERR_INVALID_ARG: return "CPDP_ERR_INVALID_ARG: W, P, ld, K or a hyperparameter out of range";
+        case CPDP_ERR_INVALID_ARG:
+            return "CPDP_ERR_INVALID_ARG: W, P, ld, K or a hyperparameter out of range";
         case CPDP_ERR_NULL: return "CPDP_ERR_NULL: a required pointer is NULL";
-        case CPDP_ERR_MISALIGNED: return "CPDP_ERR_MISALIGNED: pointer or row stride not 16-byte aligned";
+        case CPDP_ERR_MISALIGNED:
+            return "CPDP_ERR_MISALIGNED: pointer or row stride not 16-byte aligned";
         case CPDP_ERR_OVERLAP: return "CPDP_ERR_OVERLAP: argument ranges overlap";
         case CPDP_ERR_DTYPE: return "CPDP_ERR_DTYPE: unsupported storage-type combination";
         case CPDP_ERR_HIP: return "CPDP_ERR_HIP: the HIP runtime rejected the launch";

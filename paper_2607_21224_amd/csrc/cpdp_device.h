@@ -37,7 +37,7 @@
 namespace cpdp {
 namespace {
 
-// One wavefront per block.  On MI355X 64-thread blocks ran the reconcile
+// One wavefront per block (the split step: per thread group).  On MI355X 64-thread blocks ran the reconcile
 // 2.6-3.1 % and the local step 1-3.7 % faster than 256-thread blocks on the
 // fp32 ResNet-50 / ViT-S sized states (level on the 32-replica bf16 state);
 // a kernel streaming the reconcile's rows with no arithmetic gains as much,
@@ -351,7 +351,7 @@ __device__ __forceinline__ PlanView plan_view(const int64_t* plan, int64_t W, in
 // once, so 161 tensors take two dependent loads where a binary search by every
 // thread took eight, each a trip to L2 or beyond before the first data load
 // could be issued (AdamW reconcile of 4 x 271,117 coordinates in 62
-// tensors, with the split step: 14.0 -> 8.3 us).
+// tensors, not in the cache, with the split step: 13.5 -> 9.1 us).
 __device__ __forceinline__ int64_t plan_tensor(const PlanView& v, int n, int64_t b) {
     const int lane = (int)(threadIdx.x % 64);
     int lo = 0, hi = n;  // chunk_start[lo] <= b < chunk_start[hi]
@@ -397,11 +397,11 @@ __device__ __forceinline__ int64_t local_cell(int64_t cells) {
 
 // ---- step tables: the scalars of the current step read from device memory -----
 //
-// Every thread reads the position word and the entry `ahead` places past it (the same addresses for
-// the whole grid, so they are served from cache).  A position outside the
-// table means the table is used up: the kernel returns without touching the
-// state, so replaying a captured graph past its table cannot run a step with
-// undefined scalars.
+// Every thread reads the position word and the entry `ahead` places past it (the
+// same addresses for the whole grid, so they are served from cache).  A position
+// outside the table means the table is used up: the kernel returns without
+// touching the state, so replaying a captured graph past its table cannot run a
+// step with undefined scalars.
 
 // The table does not change while a step runs, so it is read through the
 // constant address space (scalar loads, which do not wait for the data).

@@ -18,8 +18,8 @@ namespace {
 // With more blocks they hide each other's chain and the wide loads get in the way
 // of the data's (2,490 blocks, 4 tensors, a state that is not in the cache: 4.49,
 // 3.92; 6.63, 5.72), but with a large table the scalar search waits longer up to
-// 6144 (600 tensors, 4,700 blocks: 7.2, 8.3; 10.5, 11.3; local
-// step of 4 replicas of 120 tensors, 2,260 blocks: 4.71, 5.33).
+// 6144 (600 tensors, 4,700 blocks: 7.2, 8.3; 10.5, 11.3; local step of 4 replicas
+// of 120 tensors, 2,260 blocks: 4.71, 5.33).
 // The split step, whose groups all search, is level or faster with the wavefront's.
 __device__ __forceinline__ int64_t plan_tensor_by_size(const PlanView& v, int W, int n,
                                                        int64_t b) {
@@ -75,8 +75,11 @@ __global__ __launch_bounds__(kBlock) void sync_plan_kernel(Src src,
 }
 
 // the split step over chunk b's tensor, for every W it takes (AdamW reconcile of
-// 4 x 271,117 coordinates in 62 tensors: 14.0 -> 8.3 us; weight decay, 8 x 23.7 M
-// in 161 tensors: 764 -> 726 us, 5.8 TB/s)
+// 4 x 271,117 coordinates in 62 tensors, not in the cache, with the search by 64
+// lanes: 13.5 -> 9.1 us; weight decay, 8 x 23.7 M in 161 tensors: 764 -> 695 us,
+// 6.0 TB/s).  The thread-per-coordinate band of the flat rows does not hold here:
+// on plans it is up to 17 % faster at 1200-2000 chunks and 4-10 % slower just past
+// 1024 and 2048 and for AdamW.
 template <Sync M, Opt O, int R, class PS, bool EXTRA, class Src>
 __global__ __launch_bounds__(kSplitThreads, split_waves(R)) void sync_plan_split_kernel(
     Src src, const int64_t* __restrict__ plan, int W, int n, float inv_w, unsigned flags) {
@@ -105,8 +108,10 @@ template <class Src>
 int local_plan_any(Opt opt, Param pt, Src src, const int64_t* plan, int W, int n,
                    int64_t total_chunks, void* stream) {
     switch (opt) {
-        case Opt::SGD_WD: return local_plan_o<Opt::SGD_WD>(pt, src, plan, W, n, total_chunks, stream);
-        case Opt::ADAMW: return local_plan_o<Opt::ADAMW>(pt, src, plan, W, n, total_chunks, stream);
+        case Opt::SGD_WD:
+            return local_plan_o<Opt::SGD_WD>(pt, src, plan, W, n, total_chunks, stream);
+        case Opt::ADAMW:
+            return local_plan_o<Opt::ADAMW>(pt, src, plan, W, n, total_chunks, stream);
         default: return local_plan_o<Opt::SGD>(pt, src, plan, W, n, total_chunks, stream);
     }
 }

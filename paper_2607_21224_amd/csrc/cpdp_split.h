@@ -14,17 +14,20 @@
 // batch's loads wait for the batch before it (its stores may alias them), so
 // it makes W/4 + 2 trips, with the update's divisions of all W replicas in a
 // row for AdamW.  Split, all loads of the block are in flight at once, the
-// whole step is one trip and three barriers, a thread needs 50 registers
-// instead of 95-226, and a block's reads are issued together before its
+// whole step is one trip and three barriers, a thread needs 54-66 registers
+// instead of 78-174, and a block's reads are issued together before its
 // writes, which the memory takes better.  Measured (us, thread-per-coordinate
-// -> split):
-//   fp32 momentum SGD, W = 8, 23.7 M coordinates      742 -> 703 (5.9 TB/s)
-//   fp32 weight decay, W = 16, 23.9 M                1511 -> 1361 (5.9 TB/s)
-//   fp32 AdamW, W = 8, 21.3 M                          933 -> 875 (5.9 TB/s)
-//   fp32 LocalSGD, W = 12, 2.8 M                       124 -> 114
-//   fp32 AdamW, W = 8, 100,003                        13.4 -> 5.5
-//   bf16 rows, W = 32, 1.0 M                            95 -> 65
-//   bf16 rows, W = 32, 100,003                          56 -> 12
+// -> split; the 100,003 with a state that is not in the cache):
+//   fp32 momentum SGD, W = 8, 23.7 M coordinates      736 -> 706 (5.9 TB/s)
+//   fp32 weight decay, W = 16, 23.9 M                1473 -> 1373 (5.9 TB/s)
+//   fp32 AdamW, W = 8, 21.3 M                          954 -> 906 (5.7 TB/s)
+//   fp32 LocalSGD, W = 12, 2.8 M                       125 -> 114
+//   fp32 AdamW, W = 8, 100,003                        16.8 -> 6.9
+//   bf16 parameters, W = 32, 2.0 M                     238 -> 189
+//   bf16 rows, W = 32, 100,003                          79 -> 14.5
+// The 100,003 also gain from the ragged loads, which the kernel on the left did
+// not have.  At sizes in between the thread-per-coordinate kernel is the faster
+// (cpdp_dispatch.h).
 #pragma once
 
 #include "cpdp_device.h"

@@ -49,7 +49,8 @@ __global__ __launch_bounds__(kBlock) void local_step_kernel(
     const int64_t p0 = (col * kBlock + threadIdx.x) * kVec;
     if (p0 >= P) return;
     const int64_t off = row * ld;
-    local_dispatch<O, PS, GS, MS>(DirectScalars{o, 0.0f, 0.0f}, params + off, mom + off, mom2 + off, grads + off, p0, P);
+    local_dispatch<O, PS, GS, MS>(DirectScalars{o, 0.0f, 0.0f}, params + off, mom + off,
+                                  mom2 + off, grads + off, p0, P);
 }
 
 template <class PS, class MS>

@@ -187,10 +187,12 @@ __global__ __launch_bounds__(kShapeMaxThreads) void shape_kernel(const int64_t* 
     if (acc == sentinel) sink[threadIdx.x % 256] = acc;
 }
 
-// ---- traffic shape in the synchronisation steps' own order -------------------
+// ---- traffic shape in the order of the thread-per-coordinate step ------------
 //
 // The same rows as the shape kernel above, loaded and stored in the order the
-// library's synchronisation kernels issue them, with no arithmetic: one
+// library's thread-per-coordinate synchronisation kernel issues them, with no
+// arithmetic (the split kernel, which takes most steps on 3 to 32 replicas, has
+// all loads of a block in flight at once and can be faster): one
 // 64-thread block per 256 coordinates, replica batches of 4, and
 //   S = 0, the reconcile: the W gradient rows in batches of 4; the anchor and
 //          the SlowMo row; per batch the momentum (and second-moment) rows
