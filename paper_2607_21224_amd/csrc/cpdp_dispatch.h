@@ -43,6 +43,7 @@ struct StepKind {
     Sync mode;
     Opt opt;
     bool bf16_params, bf16_mom;
+    bool bf16_grads = false;
 };
 
 // Wavefronts of the thread-per-coordinate kernel (64 threads of 4 coordinates).
@@ -79,11 +80,15 @@ constexpr int64_t split_round(const StepKind& k, int W) {
     return all_bf16 || (k.opt == Opt::ADAMW && W > 3) ? 8192 + 4096 : 8192;
 }
 // Wavefronts up to which.  With half the bytes a row the split step gains less and
-// the line lies higher; all-bf16 rows on many replicas have none.
+// the line lies higher; bf16 parameters and momentum on many replicas have none (us,
+// split, thread-per-coordinate: 25 x 12.0 M all-bf16 DDP 700, 595; 32 x 40.0 M
+// 2621, 2532; LocalSGD 2763, 2540), and neither has a CPDP step whose parameters
+// alone are fp32, on 17 to 30 replicas (28 x 2.6 M 231, 201; 28 x 12.0 M 1027, 960,
+// but 24 x 12.0 M 811, 830).
 constexpr int64_t column_last(const StepKind& k, int W) {
-    if (k.bf16_params && k.bf16_mom &&
-        (k.mode == Sync::CPDP ? W > 8 : W > 16 && W <= 24))
-        return INT64_MAX;
+    const bool cpdp = k.mode == Sync::CPDP;
+    if (k.bf16_params && k.bf16_mom && W > (cpdp ? 8 : 16)) return INT64_MAX;
+    if (cpdp && k.bf16_grads && k.bf16_mom && W > 16 && W <= 30) return INT64_MAX;
     if (k.opt != Opt::ADAMW && k.bf16_mom && W > 16) return 8192;
     if (k.opt != Opt::ADAMW && (k.bf16_params || k.bf16_mom)) return 5120;
     return W < 4 ? 5120 : W <= 12 ? 3328 : 3072;

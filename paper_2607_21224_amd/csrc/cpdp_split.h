@@ -198,9 +198,10 @@ __device__ __forceinline__ void split_dispatch(const Src& src, const Rows& r, fl
 }
 
 // The step as the dispatch rules see it.
-template <Sync M, Opt O, class PS, class MS = ParamF32>
+template <Sync M, Opt O, class PS, class GS = ParamF32, class MS = ParamF32>
 constexpr StepKind step_kind() {
-    return {M, O, std::is_same<PS, ParamBF16>::value, std::is_same<MS, ParamBF16>::value};
+    return {M, O, std::is_same<PS, ParamBF16>::value, std::is_same<MS, ParamBF16>::value,
+            std::is_same<GS, ParamBF16>::value};
 }
 
 // Replicas a group holds: one up to 16 groups, then two, or four where the

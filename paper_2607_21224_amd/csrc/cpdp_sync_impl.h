@@ -56,7 +56,7 @@ int sync_w(const OptParams& o, const SyncArgs& a, int resident = 0) {
 // cpdp_dispatch.h).
 template <Sync M, Opt O, class PS, class GS = ParamF32, class MS = ParamF32>
 int sync_t(const OptParams& o, const SyncArgs& a) {
-    constexpr StepKind kind = step_kind<M, O, PS, MS>();
+    constexpr StepKind kind = step_kind<M, O, PS, GS, MS>();
     const int mean_waves = ddp_mean_waves(kind, a.W, a.P, a.flags & kSyncWriteGbar);
     const bool split = can_split(a.W, blocks_for(a.P), kBlock) && mean_waves == 0 &&
                        !takes_columns(kind, a.W, a.P, a.flags != 0);

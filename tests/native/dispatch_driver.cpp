@@ -55,12 +55,13 @@ int main() {
     // other than where whole vectors end)
     for (Sync m : {Sync::CPDP, Sync::LocalSGD, Sync::DDP})
         for (Opt o : {Opt::SGD, Opt::SGD_WD, Opt::ADAMW})
-            for (int types = 0; types < 4; ++types)
+            for (int types = 0; types < 8; ++types)
                 for (int W = kSplitMinW; W <= 32; ++W) {
-                    const StepKind k{m, o, (types & 1) != 0, (types & 2) != 0};
+                    const StepKind k{m, o, (types & 1) != 0, (types & 2) != 0, (types & 4) != 0};
                     const bool none = column_last(k, W) == INT64_MAX;
-                    CHECK(none == (types == 3 && (m == Sync::CPDP ? W > 8 : W > 16 && W <= 24)),
-                          W, types);
+                    const bool many = (types & 3) == 3 && W > (m == Sync::CPDP ? 8 : 16);
+                    const bool wide = types >= 6 && m == Sync::CPDP && W > 16 && W <= 30;
+                    CHECK(none == (many || wide), W, types);
                     int turns = 0;
                     bool before = false;
                     for (int64_t waves = 1; waves < 20000; ++waves) {

@@ -75,6 +75,8 @@ def _values(st, grads, lo=0, n=None):
     (1100, 32, "cpdp", "sgd", ("f32", "bf16", "bf16"), 0),
     (1100, 24, "ddp", "sgd", ("bf16", "bf16", "bf16"), 0),
     (9000, 9, "cpdp", "sgd", ("bf16", "bf16", "bf16"), 0),
+    (9000, 28, "ddp", "sgd", ("bf16", "f32", "bf16"), 0),
+    (9000, 30, "cpdp", "sgd", ("f32", "bf16", "bf16"), 0),
     # past the cache with the gradient mean written back
     (11000, 3, "ddp", "sgd_wd", ("f32", "f32", "f32"), 1),
     (5500, 6, "ddp", "adamw", ("f32", "f32", "f32"), 3)])
