@@ -17,13 +17,18 @@ namespace {
 // replica 3.82, 3.99) and longer than 2 (4 tensors: 2.65, 2.61; 3.72, 3.69).
 // With more blocks they hide each other's chain and the wide loads get in the way
 // of the data's (2,490 blocks, 4 tensors, a state that is not in the cache: 4.49,
-// 3.92; 6.63, 5.72), but with a large table the scalar search waits longer up to
-// 6144 (600 tensors, 4,700 blocks: 7.2, 8.3; 10.5, 11.3; local step of 4 replicas
-// of 120 tensors, 2,260 blocks: 4.71, 5.33).
+// 3.92; 6.63, 5.72).  Two kinds of plan keep them up to 6144: one whose large table
+// the scalar search waits longer for (600 tensors, 4,700 blocks: 7.2, 8.3; 10.5,
+// 11.3; local step of 4 replicas of 120 tensors, 2,260 blocks: 4.71, 5.33), and one
+// of 33 to 64 tensors, which one load of 64 lanes and six scalar ones tell apart
+// (local step of 4 replicas of 62 tensors, 4,180 blocks: 4.93, 5.19 and, not in the
+// cache, 5.85, 5.77; of 2 of 120 tensors 5.37, 5.27 and 6.24, 6.07).  Decided here:
+// as a launch argument it cost the host 0.1 us.
 // The split step, whose groups all search, is level or faster with the wavefront's.
 __device__ __forceinline__ int64_t plan_tensor_by_size(const PlanView& v, int W, int n,
                                                        int64_t b) {
-    const unsigned most = (int64_t)W * n > 256 ? 6144 : 2048;
+    const bool wide = (int64_t)W * n > 256 || (n > 32 && n <= 64);
+    const unsigned most = wide ? 6144 : 2048;
     return n > 8 && gridDim.x <= most ? plan_tensor(v, n, b) : plan_tensor_scalar(v, n, b);
 }
 

@@ -159,7 +159,9 @@ def test_tables_and_plans_equal_flat_steps(W, P, opt, param, method, flags):
 
 @pytest.mark.parametrize("W,n,blocks", [(1, 1, 3), (1, 8, 40), (1, 9, 40), (2, 9, 2048),
                                         (1, 9, 2049), (1, 256, 2049), (2, 129, 2049),
-                                        (1, 257, 6144), (1, 257, 6145), (33, 10, 660)])
+                                        (1, 257, 6144), (1, 257, 6145), (33, 10, 660),
+                                        (1, 33, 2049), (2, 64, 6144), (1, 64, 6145),
+                                        (1, 65, 2049)])
 @pytest.mark.parametrize("kind", ["local", "sync"])
 def test_plan_blocks_find_their_tensors(W, n, blocks, kind):
     """Both searches of a plan, on each side of the lines between them: `blocks`
