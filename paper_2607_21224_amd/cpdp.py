@@ -284,8 +284,8 @@ def cpdp_state_init(theta0, params, mom, slow_mom, anchor, W, P, ld, K,
     s = lib.cpdp_state_init(_vec(theta0, P, "theta0", param_dt),
                             _rows(params, W, P, ld, param_dt, "params"),
                             _rows(mom, W, P, ld, mom_dt, "mom"),
-                            _vec(slow_mom, P, "slow_mom"), _vec(anchor, P, "anchor"), int(W), int(P),
-                            int(ld), int(K), _dt(param_dt), _dt(mom_dt),
+                            _vec(slow_mom, P, "slow_mom"), _vec(anchor, P, "anchor"), int(W),
+                            int(P), int(ld), int(K), _dt(param_dt), _dt(mom_dt),
                             _stream(stream))
     return _done(s, "cpdp_state_init", check)
 
@@ -314,8 +314,8 @@ def cpdp_reconcile(params, mom, grads, slow_mom, anchor, W, P, ld, K, lr, mu,
                            _span(grads, n, grad_dt, "grads"),
                            _span(slow_mom, P, CPDP_F32, "slow_mom"),
                            _span(anchor, P, CPDP_F32, "anchor"), W, P, ld, int(K),
-                           float(lr), float(mu), float(beta), float(alpha), _dt(param_dt), _dt(grad_dt),
-                           _dt(mom_dt), _stream(stream))
+                           float(lr), float(mu), float(beta), float(alpha), _dt(param_dt),
+                           _dt(grad_dt), _dt(mom_dt), _stream(stream))
     return _done(s, "cpdp_reconcile", check)
 
 
@@ -385,8 +385,9 @@ def cpdp_sync_step_opt(strategy, params, mom, mom2, grads, slow_mom, anchor, W, 
                                _span(mom2, n, CPDP_F32, "mom2"),
                                _span(grads, n, CPDP_F32, "grads"),
                                _span(slow_mom, P, CPDP_F32, "slow_mom"),
-                               _span(anchor, P, CPDP_F32, "anchor"), W, P, ld, int(K), _opt(opt), float(beta),
-                               float(alpha), int(flags), _dt(param_dt), _stream(stream))
+                               _span(anchor, P, CPDP_F32, "anchor"), W, P, ld, int(K),
+                               _opt(opt), float(beta), float(alpha), int(flags), _dt(param_dt),
+                               _stream(stream))
     return _done(s, "cpdp_sync_step_opt", check)
 
 

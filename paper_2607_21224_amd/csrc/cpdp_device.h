@@ -37,12 +37,13 @@
 namespace cpdp {
 namespace {
 
-// One wavefront per block (the split step: per thread group).  On MI355X 64-thread blocks ran the reconcile
-// 2.6-3.1 % and the local step 1-3.7 % faster than 256-thread blocks on the
-// fp32 ResNet-50 / ViT-S sized states (level on the 32-replica bf16 state);
-// a kernel streaming the reconcile's rows with no arithmetic gains as much,
-// so the difference is in how the memory system sees the blocks, not in the
-// code.  Results do not depend on it (every thread owns its 4 coordinates).
+// One wavefront per block (the split step: per thread group).  On MI355X
+// 64-thread blocks ran the thread-per-coordinate reconcile 2.6-3.1 % and the
+// local step 1-3.7 % faster than 256-thread blocks on the fp32 ResNet-50 /
+// ViT-S sized states (level on the 32-replica bf16 state); a kernel streaming
+// the reconcile's rows with no arithmetic gains as much, so the difference is
+// in how the memory system sees the blocks, not in the code.  Results do not depend
+// on it (every thread owns its 4 coordinates).
 #ifndef CPDP_BLOCK
 #define CPDP_BLOCK 64
 #endif
