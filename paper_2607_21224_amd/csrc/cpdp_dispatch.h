@@ -149,14 +149,24 @@ constexpr int ddp_mean_waves(const StepKind& k, int W, int64_t P, bool writes_me
     return P < ((int64_t)1 << 23) / W ? 0 : W == 3 ? 3 : 2;
 }
 
-// Wavefronts a SIMD that a step-table step on one and two replicas keeps resident
-// (0: as many as fit).  Its run-time-W kernel has room for six, which small and
-// mid-sized states are faster with (2 x 1,141,054 DDP: 9.3 us, 10.5 with three)
+// Wavefronts a SIMD that the run-time-W kernel keeps resident on one and two
+// replicas (0: as many as fit).  It has room for six, which small and mid-sized
+// states are faster with (step table, 2 x 1,141,054 DDP: 9.3 us, 10.5 with three)
 // and large ones slower (2 x 16.9 M CPDP 157 and 149, 2 x 15.1 M LocalSGD 110 and
 // 106).  DDP on one replica, three rows in all, keeps the six (19.7 M: 63 and 69).
-constexpr int table_waves(const StepKind& k, int W, int64_t P) {
-    if (k.mode == Sync::DDP && W == 1) return 0;
-    return W < kSplitMinW && P >= ((int64_t)1 << 24) / W ? 3 : 0;
+// AdamW keeps as many as fit in plans and variants (plan, 1 x 30 M DDP: 133 us, 141
+// when its registers left room for fewer).
+// A plan's kernel has room for eight (LocalSGD six) and is best with three only on
+// two replicas that are averaged (us with all, three: CPDP 2 x 18.0 M 167, 161;
+// 1 x 30 M 179, 181, with five 173; LocalSGD 2 x 20.0 M 148, 140; 1 x 40 M 152,
+// 169, with five 154; DDP 2 x 20.0 M 133, 132, with six 129).
+enum class RunTime { Table, Plan, Variant };
+constexpr int run_time_waves(const StepKind& k, int W, int64_t P, RunTime kernel) {
+    if (W >= kSplitMinW || P < ((int64_t)1 << 24) / W) return 0;
+    if (k.opt == Opt::ADAMW && kernel != RunTime::Table) return 0;
+    if (kernel == RunTime::Plan && k.mode == Sync::DDP) return 6;
+    if (kernel == RunTime::Plan && W == 1) return 5;
+    return k.mode == Sync::DDP && W == 1 ? 0 : 3;
 }
 
 }  // namespace cpdp

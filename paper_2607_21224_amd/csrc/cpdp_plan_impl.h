@@ -134,11 +134,13 @@ int sync_plan_t(Src src, const int64_t* plan, int W, int n, int64_t total_chunks
                                              total_chunks, W, R, stream, src, plan, W, n, inv_w,
                                              flags);
         });
+    const int resident =
+        run_time_waves(step_kind<M, O, PS>(), W, total_chunks * kCoords, RunTime::Plan);
     if (flags != 0)
-        return launch(sync_plan_kernel<M, O, PS, true, Src>, total_chunks, stream, src, plan, W,
-                      n, inv_w, flags);
-    return launch(sync_plan_kernel<M, O, PS, false, Src>, total_chunks, stream, src, plan, W, n,
-                  inv_w, flags);
+        return launch_resident(resident, sync_plan_kernel<M, O, PS, true, Src>, total_chunks,
+                               stream, src, plan, W, n, inv_w, flags);
+    return launch_resident(resident, sync_plan_kernel<M, O, PS, false, Src>, total_chunks,
+                           stream, src, plan, W, n, inv_w, flags);
 }
 
 template <Sync M, Opt O, class Src>

@@ -62,9 +62,12 @@ int sync_t(const OptParams& o, const SyncArgs& a) {
                        !takes_columns(kind, a.W, a.P, a.flags != 0);
     const DirectScalars src{o, a.beta, a.alpha * o.lr};
     if constexpr (std::is_same<GS, ParamF32>::value && std::is_same<MS, ParamF32>::value) {
-        if (a.flags != 0)
+        if (a.flags != 0) {
+            const int resident =
+                mean_waves != 0 ? mean_waves : run_time_waves(kind, a.W, a.P, RunTime::Variant);
             return split ? sync_split<M, O, PS, true, GS, MS>(src, a)
-                         : sync_w<M, O, 0, PS, true>(o, a, mean_waves);
+                         : sync_w<M, O, 0, PS, true>(o, a, resident);
+        }
     }
     if (split) return sync_split<M, O, PS, false, GS, MS>(src, a);
     if (a.W == 1) return sync_w<M, O, 1, PS, false, GS, MS>(o, a);

@@ -114,7 +114,7 @@ int sync_table_t(const TableScalars& src, const SyncArgs& a) {
     }
     // step tables take fp32 gradients
     const float* grads = static_cast<const float*>(a.grads);
-    const int resident = table_waves(step_kind<M, O, PS>(), a.W, a.P);
+    const int resident = run_time_waves(step_kind<M, O, PS>(), a.W, a.P, RunTime::Table);
     if (a.flags != 0)
         return launch_resident(resident, sync_table_kernel<M, O, PS, true>, blocks_for(a.P),
                                a.stream, src.table, src.ahead, static_cast<T*>(a.params),

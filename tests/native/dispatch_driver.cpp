@@ -89,6 +89,18 @@ int main() {
                     CHECK(takes_columns({Sync::CPDP, Opt::SGD, false, false}, 8, 4096, false), 8, 4096);
                     CHECK(!takes_columns({Sync::CPDP, Opt::SGD, false, false}, 8, 4097, false), 8, 4097);
                 }
+    // wavefronts of the run-time-W kernel: large states of one and two replicas only
+    const StepKind sgd{Sync::CPDP, Opt::SGD, false, false}, adam{Sync::CPDP, Opt::ADAMW, false, false};
+    const StepKind ddp{Sync::DDP, Opt::SGD, false, false};
+    for (RunTime r : {RunTime::Table, RunTime::Plan, RunTime::Variant})
+        for (int W = 1; W <= 40; ++W) {
+            const int64_t large = ((int64_t)1 << 24) / W;
+            const bool plan = r == RunTime::Plan, few = W <= 2;
+            CHECK(run_time_waves(sgd, W, large - 1, r) == 0, W, large - 1);
+            CHECK(run_time_waves(sgd, W, large, r) == (!few ? 0 : plan && W == 1 ? 5 : 3), W, large);
+            CHECK(run_time_waves(adam, W, large, r) == (few && r == RunTime::Table ? 3 : 0), W, large);
+            CHECK(run_time_waves(ddp, W, large, r) == (!few ? 0 : plan ? 6 : W == 2 ? 3 : 0), W, large);
+        }
     std::printf("%s\n", failures ? "FAILED" : "OK");
     return failures ? 1 : 0;
 }
